@@ -1040,6 +1040,17 @@ __global__ __launch_bounds__(kTile * kCutWaves) void k_cut_items(
     write_cut_items(m1, w, lane, off1, out1, cap);
 }
 
+// Inclusive sum of v over the lanes of a full wave.
+__device__ __forceinline__ int wave_scan(int v, int lane)
+{
+#pragma unroll
+    for (int d = 1; d < kTile; d <<= 1) {
+        const int o = from_lane_i(v, (lane - d) & (kTile - 1));
+        v += lane >= d ? o : 0;
+    }
+    return v;
+}
+
 // ================================================================ pass 1
 // I_i = sum_{j != i} H(r_ij; rt_i, S_j) over every unordered pair once.
 
@@ -1168,49 +1179,40 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
         // terms through LDS integer atomics, i-side terms back to the i lane
         bool deferred = false;
         if constexpr (DEFER) {
-            deferred = __builtin_amdgcn_ballot_w64(dmask != 0ull) != 0ull;
+            const int cnt = __builtin_popcountll(dmask);
+            deferred = __builtin_amdgcn_ballot_w64(cnt != 0) != 0ull;
             if (deferred) {
                 sdef[lane] = 0ull;
-                wave_sync();
-                for (;;) {
-                    const int cnt = __builtin_popcountll(dmask);
-                    int incl = cnt;
-#pragma unroll
-                    for (int dd = 1; dd < kTile; dd <<= 1) {
-                        const int o = from_lane_i(incl, (lane - dd) & (kTile - 1));
-                        incl += lane >= dd ? o : 0;
-                    }
-                    const int total = __builtin_amdgcn_readlane(incl, kTile - 1);
-                    if (total == 0) break;
-                    const int o0 = incl - cnt;
-                    const int n = o0 < kTile ? min(cnt, kTile - o0) : 0;
+                T* siv = sS + kTile;
+                const int incl = wave_scan(cnt, lane);
+                const int total = __builtin_amdgcn_readlane(incl, kTile - 1);
+                for (int w0 = 0; w0 < total; w0 += kTile) {
+                    const int o0 = max(incl - cnt, w0) - w0;
+                    const int n = max(min(incl, w0 + kTile) - w0 - o0, 0);
                     for (int t = o0; t < o0 + n; ++t) {
                         const int k = __builtin_ctzll(dmask);
                         dmask &= dmask - 1ull;
                         slist[t] = (lane << 8) | k;
                     }
                     wave_sync();
-                    T iv = T(0);
-                    if (lane < total) {
-                        const int e = slist[lane], il = e >> 8, k = e & 0xff;
-                        const int gi = w.base + w.I * kTile + il;
-                        const Q4<T> pi = P[gi];
-                        const Q4<T> gxi = Gx[gi];       // rt, S
-                        const JD d = load(il + k);
-                        const T dx = pi.x - d.p.x, dy = pi.y - d.p.y, dz = pi.z - d.p.z;
+                    const bool on = w0 + lane < total;
+                    const int e = on ? slist[lane] : 0, il = e >> 8;
+                    const int jl = (il + (e & 0xff)) & (kTile - 1);
+                    const T px = from_lane(xi[0], il), py = from_lane(yi[0], il);
+                    const T pz = from_lane(zi[0], il), prt = from_lane(rti[0], il);
+                    const T pS = from_lane(Si[0], il);
+                    if (on) {
+                        const JD d = load(jl);
+                        const T dx = px - d.p.x, dy = py - d.p.y, dz = pz - d.p.z;
                         const T r2 = dx * dx + dy * dy + dz * dz;
                         const T invr = rsq(r2);
                         const T rr = r2 * invr;
-                        iv = slow_H(rr, invr, gxi.x, d.S);              // H(r; rt_i, S_j)
-                        const T hv = slow_H(rr, invr, d.p.w, gxi.y);    // H(r; rt_j, S_i)
-                        atomicAdd(&sdef[(il + k) & (kTile - 1)],
-                                  (unsigned long long)to_fixed(hv, kScaleI, bad));
-                    }
-                    for (int u = 0; __builtin_amdgcn_ballot_w64(u < n) != 0ull; ++u) {
-                        const T v = from_lane(iv, min(o0 + u, kTile - 1));
-                        if (u < n) ai[0] += v;
+                        siv[lane] = slow_H(rr, invr, prt, d.S);         // H(r; rt_i, S_j)
+                        const T hv = slow_H(rr, invr, d.p.w, pS);       // H(r; rt_j, S_i)
+                        atomicAdd(&sdef[jl], (unsigned long long)to_fixed(hv, kScaleI, bad));
                     }
                     wave_sync();
+                    for (int u = 0; u < n; ++u) ai[0] += siv[o0 + u];
                 }
             }
         }
@@ -1780,8 +1782,7 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
                                dri[r], acc[3]);
             } else if constexpr (DEFER) {
                 // only pairs of a real i atom are marked (padding lanes sit far
-                // apart, so none of theirs needs the closed form anyway); the
-                // packed rounds read the i atom back from global memory
+                // apart, so none of theirs needs the closed form anyway)
                 chain_pair_fast<!SEP>(rr, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, act && vi[r],
                                       1ull << kstep, dEdr, gij2, gji2, dmask[r]);
                 if (r == R - 1) ++kstep;            // a step serves every row of the item
@@ -1825,32 +1826,31 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
         // of a round's lanes does not matter); the i-side terms go back to the
         // i atom's lane, which owns a contiguous run of the round's entries
         // (its first row's marks, then its second row's), and join its FP32
-        // sums in list order.
+        // sums in list order.  A round is a chain of latencies, not of work
+        // (a wave waits for it alone), so it stays on the CU: the i atom comes
+        // from its lane's registers (ds_bpermute), the list offsets from one
+        // scan over the lanes before the rounds, and the i-side terms pass
+        // through the second copy of the j block, which is not needed after
+        // the walk (one 256-atom globule 75.1 -> 72.0 us per evaluation, one
+        // 3,001-atom one 80.9 -> 79.0, against a scan per round and the i atom
+        // read back from global memory).
         bool deferred = false;
         if constexpr (DEFER) {
-            unsigned long long any = 0ull;
-#pragma unroll
-            for (int r = 0; r < R; ++r) any |= dmask[r];
-            deferred = __builtin_amdgcn_ballot_w64(any != 0ull) != 0ull;
+            const int cnt0 = __builtin_popcountll(dmask[0]);
+            const int cnt = R == 1 ? cnt0 : cnt0 + __builtin_popcountll(dmask[R - 1]);
+            deferred = __builtin_amdgcn_ballot_w64(cnt != 0) != 0ull;
             if (deferred) {
 #pragma unroll
                 for (int a = 0; a < 4; ++a) sdef[a * kTile + lane] = 0ull;
-                wave_sync();
-                for (;;) {
-                    const int cnt0 = __builtin_popcountll(dmask[0]);
-                    const int cnt = R == 1 ? cnt0 : cnt0 + __builtin_popcountll(dmask[R - 1]);
-                    int incl = cnt;                     // inclusive scan over the lanes
-#pragma unroll
-                    for (int d = 1; d < kTile; d <<= 1) {
-                        const int o = from_lane_i(incl, (lane - d) & (kTile - 1));
-                        incl += lane >= d ? o : 0;
-                    }
-                    const int total = __builtin_amdgcn_readlane(incl, kTile - 1);
-                    if (total == 0) break;
-                    // this lane's entries of the round: list slots [o0, o0 + n)
-                    const int o0 = incl - cnt;
-                    const int n = o0 < kTile ? min(cnt, kTile - o0) : 0;
-                    const int n0 = min(n, cnt0);        // entries [0, n0) of the run: first row
+                Q4<T>* siv = sj + kTile;
+                const int incl = wave_scan(cnt, lane);
+                const int total = __builtin_amdgcn_readlane(incl, kTile - 1);
+                for (int w0 = 0; w0 < total; w0 += kTile) {
+                    // this lane's entries of the round: list slots [o0, o0 + n),
+                    // the first n0 of them its first row's
+                    const int o0 = max(incl - cnt, w0) - w0;
+                    const int n = max(min(incl, w0 + kTile) - w0 - o0, 0);
+                    const int n0 = min(n, (int)__builtin_popcountll(dmask[0]));
                     for (int t = o0; t < o0 + n; ++t) {
                         int k, ir;
                         if (R == 1 || dmask[0] != 0ull) {
@@ -1865,53 +1865,51 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
                         slist[t] = (lane << 8) | (ir << 7) | k;
                     }
                     wave_sync();
-                    T iv[4] = {T(0), T(0), T(0), T(0)};
-                    if (lane < total) {
-                        const int e = slist[lane], il = e >> 8, k = e & 0x7f;
-                        const int gi = w.base + (w.I + ((e >> 7) & 1)) * kTile + il;
-                        const Q4<T> pi = P[gi];
-                        const Q4<T> gxi = Gx[gi];       // rt, S, screen
-                        const T bi_ = brt_from<T>(ld_dev(wk.G_fx + gi),
-                                                  ld_dev(wk.dRdPsi_p + gi), gxi.x);
-                        const JD d = load(il + k);
+                    const bool on = w0 + lane < total;
+                    const int e = on ? slist[lane] : 0, il = e >> 8;
+                    const int jl = (il + (e & 0x7f)) & (kTile - 1);
+                    const bool second = R == 2 && (e & 0x80);
+                    // (every lane takes part in the cross-lane reads)
+                    auto of_i = [&](const T (&v)[R]) {
+                        const T a = from_lane(v[0], il);
+                        if constexpr (R == 1) return a;
+                        const T b = from_lane(v[R - 1], il);
+                        return second ? b : a;
+                    };
+                    const T px = of_i(xi), py = of_i(yi), pz = of_i(zi);
+                    const T prt = of_i(rti), pS = of_i(Si), ps = of_i(si), bi_ = of_i(Bi);
+                    if (on) {
+                        const JD d = load(jl);
                         const Q4<T>& p = d.p;
                         const Q4<T>& b = d.b;
-                        const T dx = pi.x - p.x, dy = pi.y - p.y, dz = pi.z - p.z;
+                        const T dx = px - p.x, dy = py - p.y, dz = pz - p.z;
                         const T r2 = dx * dx + dy * dy + dz * dz;
                         const T invr = rsq(r2);
                         const T rr = r2 * invr;
                         T ga[3], gb[3];
-                        slow_grad(rr, invr, gxi.x, b.x, ga);            // H(r; rt_i, S_j)
-                        slow_grad(rr, invr, p.w, gxi.y, gb);            // H(r; rt_j, S_i)
+                        slow_grad(rr, invr, prt, b.x, ga);              // H(r; rt_i, S_j)
+                        slow_grad(rr, invr, p.w, pS, gb);               // H(r; rt_j, S_i)
                         const T bj_ = b.y;
                         // dE/dr = bi dH_ij/dr + bj dH_ji/dr
                         const T fr = T(fma(bi_, ga[0], bj_ * gb[0])) * invr;
                         const T fx = fr * dx, fy = fr * dy, fz = fr * dz;
-                        iv[0] = -fx; iv[1] = -fy; iv[2] = -fz;
-                        iv[3] = T(fma(bi_, ga[1], gxi.z * bj_ * gb[2]));
+                        siv[lane] = Q4<T>{-fx, -fy, -fz, T(fma(bi_, ga[1], ps * bj_ * gb[2]))};
                         const T jv[4] = {fx, fy, fz, T(fma(b.z * bi_, ga[2], bj_ * gb[1]))};
-                        const int jl = (il + k) & (kTile - 1);
 #pragma unroll
                         for (int a = 0; a < 4; ++a)
                             atomicAdd(&sdef[a * kTile + jl],
                                       (unsigned long long)to_fixed(jv[a], kScaleF, bad));
                     }
-                    // i side: every lane reads its run (all lanes take part in
-                    // each read, the sums only for u < n)
-                    for (int u = 0; __builtin_amdgcn_ballot_w64(u < n) != 0ull; ++u) {
-                        const int src = min(o0 + u, kTile - 1);
-                        const T v0 = from_lane(iv[0], src), v1 = from_lane(iv[1], src);
-                        const T v2 = from_lane(iv[2], src), v3 = from_lane(iv[3], src);
-                        if (u < n) {
-                            if (R == 1 || u < n0) {
-                                fxi[0] += v0; fyi[0] += v1; fzi[0] += v2; dri[0] += v3;
-                            } else {
-                                fxi[R - 1] += v0; fyi[R - 1] += v1; fzi[R - 1] += v2;
-                                dri[R - 1] += v3;
-                            }
+                    wave_sync();
+                    for (int u = 0; u < n; ++u) {
+                        const Q4<T> v = siv[o0 + u];
+                        if (R == 1 || u < n0) {
+                            fxi[0] += v.x; fyi[0] += v.y; fzi[0] += v.z; dri[0] += v.w;
+                        } else {
+                            fxi[R - 1] += v.x; fyi[R - 1] += v.y; fzi[R - 1] += v.z;
+                            dri[R - 1] += v.w;
                         }
                     }
-                    wave_sync();
                 }
             }
         }
