@@ -75,6 +75,8 @@ struct gbmc_plan {
     int spin_limit = kDefaultSpinLimit;   // polls before a wait of a queued launch gives up
     int32_t n_chunks = 0;            // cutoff passes: block rows in chunks of 64 j blocks
     WorkItem* d_chunks = nullptr;
+    int32_t n_sums = 0;              // spans of the energy sums
+    SumSpan* d_sums = nullptr;       // [n_sums], then the same systems as one span each [n_sys]
     int device = 0;
     void* scratch = nullptr;         // the library's static scratch on `device`
     hipError_t scratch_err = hipSuccess;
@@ -496,6 +498,21 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
             delete p;
             return fail(GBMC_ERR_UNSUPPORTED, "too many blocks for the cutoff work lists");
         }
+        // energy sums: spans of kSumAtoms atoms (a system of several has at least
+        // 65 blocks, hence 195 words of qcnt for its five); after them one span
+        // per system, for the queued launch, whose counters live in qcnt
+        std::vector<SumSpan> sums, whole;
+        for (int32_t b = 0, blk0 = 0; b < n_systems; ++b) {
+            const int32_t a0 = host_atom_offset[b], a1 = host_atom_offset[b + 1];
+            const int32_t n = std::max(1, (a1 - a0 + kSumAtoms - 1) / kSumAtoms);
+            for (int32_t k = 0; k < n; ++k)
+                sums.push_back(SumSpan{b, a0 + k * kSumAtoms, k + 1 < n ? a0 + (k + 1) * kSumAtoms : a1,
+                                       n, (3 * blk0 + 1) & ~1});
+            whole.push_back(SumSpan{b, a0, a1, 1, 0});
+            blk0 += (a1 - a0 + kTile - 1) / kTile;
+        }
+        p->n_sums = (int32_t)sums.size();
+        sums.insert(sums.end(), whole.begin(), whole.end());
         p->n_chunks = (int32_t)chunks.size();
         p->cut_cap = p->n_chunks * (kCutChunk / kCutTiles);
         layout(p);
@@ -521,7 +538,8 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
         const size_t at_blk = align256(at_off + off_bytes);
         const size_t at_chk = align256(at_blk + sizeof(BlockSpan) * blocks.size());
         const size_t at_tot = align256(at_chk + sizeof(WorkItem) * chunks.size());
-        const size_t total = at_tot + sizeof(int32_t) * totals.size();
+        const size_t at_sum = align256(at_tot + sizeof(int32_t) * totals.size());
+        const size_t total = at_sum + sizeof(SumSpan) * sums.size();
         if (total > 0) {
             char* d = nullptr;
             e = hipMalloc(&d, total);
@@ -547,6 +565,9 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
             p->d_total = reinterpret_cast<int32_t*>(d + at_tot);
             if (!totals.empty())
                 std::memcpy(h.data() + at_tot, totals.data(), sizeof(int32_t) * totals.size());
+            p->d_sums = reinterpret_cast<SumSpan*>(d + at_sum);
+            if (!sums.empty())
+                std::memcpy(h.data() + at_sum, sums.data(), sizeof(SumSpan) * sums.size());
             e = hipMemcpy(d, h.data(), h.size(), hipMemcpyHostToDevice);
             if (e != hipSuccess) { (void)hipFree(d); delete p; return hip_fail(e, "hipMemcpy(plan tables)"); }
         }
@@ -794,7 +815,8 @@ static hipError_t run_queued(gbmc_plan* p, const gbmc_atoms* a, const GBConst& c
     int n = 0;
     for (int k = 0; k < GBMC_N_PASSES; ++k) n += p->n_items[k];
     hipEvent_t* ev = n > 0 ? events(p, {id}) : nullptr;
-    return launch_queued<T>(queue_shape(p), p->n_atoms, p->n_sys, (const T*)a->x, (const T*)a->y,
+    return launch_queued<T>(queue_shape(p), p->n_atoms, p->d_sums + p->n_sums, p->n_sys,
+                            (const T*)a->x, (const T*)a->y,
                             (const T*)a->z, (const T*)a->q, (const T*)a->rho,
                             (const T*)a->screen, c, carve<T>(p, ws), (T*)born_R, e_coul, e_gb,
                             (T*)force, (T*)dEdq, (T*)dEdrho, s, ev, id);
@@ -842,13 +864,13 @@ static hipError_t energy_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst
                        p->tuning.waves_per_group[GBMC_PASS_CHAIN],
                        p->tuning.j_blocks_per_item[GBMC_PASS_CHAIN] == 1};
     if (p->prec == GBMC_FP32_FIXED)
-        return launch_energy_forces<float>(pe, pc, p->n_atoms, p->n_sys, cut_plan(p),
+        return launch_energy_forces<float>(pe, pc, p->n_atoms, p->d_sums, p->n_sums, cut_plan(p),
                                            (const float*)a->x, (const float*)a->y,
                                            (const float*)a->z, (const float*)a->q,
                                            (const float*)a->rho, (const float*)a->screen, c,
                                            carve<float>(p, ws), e_coul, e_gb, (float*)force,
                                            (float*)dEdq, (float*)dEdrho, s, ev, staged);
-    return launch_energy_forces<double>(pe, pc, p->n_atoms, p->n_sys, cut_plan(p),
+    return launch_energy_forces<double>(pe, pc, p->n_atoms, p->d_sums, p->n_sums, cut_plan(p),
                                         (const double*)a->x, (const double*)a->y,
                                         (const double*)a->z, (const double*)a->q,
                                         (const double*)a->rho, (const double*)a->screen, c,

@@ -53,6 +53,14 @@ struct CutItem {
 constexpr int kCutTiles = 4;
 constexpr int kCutChunk = 64;            // j blocks per chunk of a block row
 
+// Atoms [a0, a1) of system `sys` whose energy shares one workgroup of the output
+// kernels sums; the system has n of these, and its two partial sums and their
+// count start at word `slot` (even) of qcnt.
+struct SumSpan {
+    int32_t sys, a0, a1, n, slot;
+};
+constexpr int kSumAtoms = 4096;
+
 // Static tables of the cutoff passes: the 64-atom blocks of the batch and the
 // chunks of 64 j blocks of every block row that the compaction kernel scans.
 struct CutPlan {
@@ -107,7 +115,8 @@ struct Work {
                                   //  launch gave up (both since the last radii call)
     int* qhead;                   // [kQueueWords]: ticket counter ([0]) and error word ([32])
                                   //  of the queued launch
-    int* qcnt;                    // [3][n_blocks]: per-block item counters of the passes
+    int* qcnt;                    // [3][n_blocks]: per-block item counters of the queued
+                                  //  launch; otherwise the partial energy sums (SumSpan)
     Q4<float>* bnd;               // [n_blocks] bounding sphere of each block: centre, radius
     float* smax;                  // [n_blocks] largest S = screen (rho - offset) of each block
     Q4<float>* box;               // [2][n_blocks] coordinate box of each block (processing
@@ -206,7 +215,7 @@ struct PassShape {
 
 template <typename T>
 hipError_t launch_energy_forces(const PassShape& energy, const PassShape& chain, int n_atoms,
-                                int n_sys, const CutPlan& cp,
+                                const SumSpan* sums, int n_sums, const CutPlan& cp,
                                 const T* x, const T* y, const T* z, const T* q, const T* rho,
                                 const T* screen, const GBConst& c, const Work<T>& w,
                                 double* e_coul, double* e_gb, T* force, T* dEdq, T* dEdrho,
@@ -232,7 +241,8 @@ struct QueueShape {
 // Staging, the three all-pairs passes (descreening, energy / explicit
 // forces with gradients, Born chain) in one queued launch, and the outputs.
 template <typename T>
-hipError_t launch_queued(const QueueShape& sh, int n_atoms, int n_sys, const T* x, const T* y,
+hipError_t launch_queued(const QueueShape& sh, int n_atoms, const SumSpan* sums, int n_sums,
+                         const T* x, const T* y,
                          const T* z, const T* q, const T* rho, const T* screen, const GBConst& c,
                          const Work<T>& w, T* born_R, double* e_coul, double* e_gb, T* force,
                          T* dEdq, T* dEdrho, hipStream_t s, hipEvent_t* ev, int timing_id);
