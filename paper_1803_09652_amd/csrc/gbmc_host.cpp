@@ -49,6 +49,23 @@ const gbmc_tuning kDefaultTuning32 = {{1, 1, 1}, {2, 4, 4}};
 const gbmc_tuning kDefaultTuning64 = {{1, 1, 1}, {2, 2, 2}};
 constexpr int64_t kLongItemTiles = int64_t(1) << 19;
 
+// The most (single-tile) items for which a pass of a plan with the default
+// shapes runs one workgroup per item (gbmc_wide.h) instead of one wavefront.
+// Results are bitwise the same; the line lies where the launches took equally
+// long (us, wavefront / workgroup per item; an item of the FP32 energy and chain
+// passes has two rows):
+//   FP32 descreening  820 items 14.8 / 10.6, 1128 14.6 / 12.4, 2016 14.9 / 15.7
+//   FP32 energy       168 17.2 / 11.7,  288 17.8 / 15.6,  440 18.3 / 20.3
+//   FP32 chain        599 28.8 / 22.6,  704 29.1 / 18.4, 1055 29.0 / 29.7
+//   FP64 descreening  820 24.3 / 18.5, 1128 24.3 / 20.5, 2016 26.3 / 29.0
+//   FP64 energy       136 16.8 / 15.6,  288 17.1 / 19.0
+//   FP64 chain        820 32.9 / 26.6, 1128 33.0 / 31.8, 2016 36.3 / 49.7
+int64_t wide_items(gbmc_precision prec, int pass)
+{
+    static const int64_t most[2][GBMC_N_PASSES] = {{1536, 320, 896}, {1536, 192, 1152}};
+    return most[prec == GBMC_FP64 ? 1 : 0][pass];
+}
+
 // Queued launch: the polls (each after a short sleep, about a microsecond
 // apiece) before a dependency wait gives up: seconds, far beyond any wait the
 // schedule produces.
@@ -61,6 +78,7 @@ struct gbmc_plan {
     int32_t n_atoms = 0;
     gbmc_precision prec = GBMC_FP32_FIXED;
     gbmc_tuning tuning = kDefaultTuning32;
+    bool wide[GBMC_N_PASSES] = {false, false, false};   // pass runs one workgroup per item
     std::vector<int32_t> offset;     // [B+1]
     int32_t n_items[GBMC_N_PASSES] = {0, 0, 0};
     WorkItem* d_items[GBMC_N_PASSES] = {nullptr, nullptr, nullptr};
@@ -479,6 +497,8 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
         p->n_atoms = n_systems > 0 ? host_atom_offset[n_systems] : 0;
         p->prec = precision;
         p->tuning = t;
+        for (int k = 0; k < GBMC_N_PASSES; ++k)
+            p->wide[k] = !tuning && (int64_t)items[k].size() <= wide_items(precision, k);
         p->offset.assign(host_atom_offset, host_atom_offset + n_systems + 1);
         if (n_systems == 0) p->offset.assign(1, 0);
         std::vector<BlockSpan> blocks;
@@ -787,6 +807,12 @@ static hipEvent_t* events(gbmc_plan* p, std::initializer_list<int> ids)
 
 static bool uses_cutoffs(const GBConst& c) { return c.rgbmax > 0.0 || c.cutoff > 0.0; }
 
+static PassShape pass_shape(const gbmc_plan* p, int k)
+{
+    return PassShape{p->d_items[k], p->n_items[k], p->tuning.waves_per_group[k],
+                     p->tuning.j_blocks_per_item[k] == 1, p->wide[k]};
+}
+
 static QueueShape queue_shape(const gbmc_plan* p)
 {
     QueueShape sh{};
@@ -832,16 +858,14 @@ static hipError_t radii_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst&
 {
     hipEvent_t* ev = p->n_items[GBMC_PASS_RADII] > 0 ? events(p, {kKRadii}) : nullptr;
     if (p->prec == GBMC_FP32_FIXED)
-        return launch_radii<float>(p->d_items[GBMC_PASS_RADII], p->n_items[GBMC_PASS_RADII],
-                                   p->tuning.waves_per_group[GBMC_PASS_RADII], p->n_atoms,
-                                   cut_plan(p), (const float*)a->x, (const float*)a->y,
+        return launch_radii<float>(pass_shape(p, GBMC_PASS_RADII), p->n_atoms, cut_plan(p),
+                                   (const float*)a->x, (const float*)a->y,
                                    (const float*)a->z, (const float*)a->rho,
                                    (const float*)a->screen, c, carve<float>(p, ws),
                                    (float*)born_R, s, ev,
                                    with_q ? (const float*)a->q : nullptr);
-    return launch_radii<double>(p->d_items[GBMC_PASS_RADII], p->n_items[GBMC_PASS_RADII],
-                                p->tuning.waves_per_group[GBMC_PASS_RADII], p->n_atoms,
-                                cut_plan(p), (const double*)a->x, (const double*)a->y,
+    return launch_radii<double>(pass_shape(p, GBMC_PASS_RADII), p->n_atoms, cut_plan(p),
+                                (const double*)a->x, (const double*)a->y,
                                 (const double*)a->z, (const double*)a->rho,
                                 (const double*)a->screen, c, carve<double>(p, ws),
                                 (double*)born_R, s, ev, with_q ? (const double*)a->q : nullptr);
@@ -857,12 +881,7 @@ static hipError_t energy_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst
     hipEvent_t* ev = nullptr;
     if (p->n_items[GBMC_PASS_ENERGY] > 0)
         ev = chain ? events(p, {kKEnergy, kKChain}) : events(p, {kKEnergy});
-    const PassShape pe{p->d_items[GBMC_PASS_ENERGY], p->n_items[GBMC_PASS_ENERGY],
-                       p->tuning.waves_per_group[GBMC_PASS_ENERGY],
-                       p->tuning.j_blocks_per_item[GBMC_PASS_ENERGY] == 1};
-    const PassShape pc{p->d_items[GBMC_PASS_CHAIN], p->n_items[GBMC_PASS_CHAIN],
-                       p->tuning.waves_per_group[GBMC_PASS_CHAIN],
-                       p->tuning.j_blocks_per_item[GBMC_PASS_CHAIN] == 1};
+    const PassShape pe = pass_shape(p, GBMC_PASS_ENERGY), pc = pass_shape(p, GBMC_PASS_CHAIN);
     if (p->prec == GBMC_FP32_FIXED)
         return launch_energy_forces<float>(pe, pc, p->n_atoms, p->d_sums, p->n_sums, cut_plan(p),
                                            (const float*)a->x, (const float*)a->y,

@@ -200,19 +200,19 @@ enum KernelId { kKRadii = 0, kKEnergy = 1, kKChain = 2, kKSiteRows = 3, kKSiteDE
 // Launchers (gbmc_kernels.hip).  All return hipSuccess or the launch error.
 // ev (nullable) holds 2 * kNumKernels events: the start and stop events bound to
 // the dispatch of each timed kernel.
-template <typename T>
-hipError_t launch_radii(const WorkItem* items, int n_items, int waves_per_group, int n_atoms,
-                        const CutPlan& cp,
-                        const T* x, const T* y, const T* z, const T* rho, const T* screen,
-                        const GBConst& c, const Work<T>& w, T* born_R, hipStream_t s,
-                        hipEvent_t* ev, const T* q = nullptr);
 struct PassShape {
     const WorkItem* items;
     int n_items;
     int waves_per_group;
     bool one_tile;          // every item is a single tile (one j block per item)
+    bool wide;              // one workgroup per item (gbmc_wide.h; single tiles, all pairs)
 };
 
+template <typename T>
+hipError_t launch_radii(const PassShape& radii, int n_atoms, const CutPlan& cp,
+                        const T* x, const T* y, const T* z, const T* rho, const T* screen,
+                        const GBConst& c, const Work<T>& w, T* born_R, hipStream_t s,
+                        hipEvent_t* ev, const T* q = nullptr);
 template <typename T>
 hipError_t launch_energy_forces(const PassShape& energy, const PassShape& chain, int n_atoms,
                                 const SumSpan* sums, int n_sums, const CutPlan& cp,

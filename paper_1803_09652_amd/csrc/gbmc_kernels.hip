@@ -265,11 +265,18 @@ __device__ __forceinline__ float hct_slow32(float r, float invr, float rt, float
     return zero ? 0.0f : H;
 }
 
+// dx^2 + dy^2 + dz^2 in a fixed order of operations.  Left to the compiler, the
+// products it fuses differ from loop to loop, and with them the last bit.
+template <typename T>
+__device__ __forceinline__ T dist2(T dx, T dy, T dz)
+{
+    return fma(dz, dz, fma(dx, dx, dy * dy));
+}
+
 __device__ __forceinline__ void dist64(double xi, double yi, double zi, double xj, double yj,
                                        double zj, double& r, double& invr)
 {
-    double dx = xi - xj, dy = yi - yj, dz = zi - zj;
-    double r2 = dx * dx + dy * dy + dz * dz;
+    const double r2 = dist2(xi - xj, yi - yj, zi - zj);
     invr = rsq64(r2);
     r = r2 * invr;
 }
@@ -922,10 +929,19 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Whether r^2 of a pair starts with x^2 instead of y^2 in the energy pass: in the
+// odd steps of a diagonal tile but the last (the order in which the walk was
+// first compiled, kept so that energies stay the same to the last bit).
+__device__ __forceinline__ constexpr bool energy_xfirst(bool diagonal, int k)
+{
+    return diagonal && (k & 1) && k < kTile / 2 - 1;
+}
+
 // Walks the steps of one tile.  load(s) fetches the j data at LDS slot s;
 // pair(d, r, act, acc_j) evaluates the pair of this lane's i row r with that j
 // and adds the j-side terms to acc_j (NJ sums); act is false only for the
-// lanes that must skip a duplicated pair.  On return acc_j of lane l holds the
+// lanes that must skip a duplicated pair, and xfirst tells energy_xfirst of the
+// step.  On return acc_j of lane l holds the
 // sums of j = 64 J + l.
 template <typename T, int NJ, class Load, class Pair>
 __device__ __forceinline__ void walk_tile(int lane, bool diagonal, T (&acc_j)[NJ], Load&& load,
@@ -933,8 +949,8 @@ __device__ __forceinline__ void walk_tile(int lane, bool diagonal, T (&acc_j)[NJ
 {
 #pragma unroll
     for (int a = 0; a < NJ; ++a) acc_j[a] = T(0);
-    auto step = [&](const auto& d, bool valid) {
-        pair(d, 0, valid, acc_j);
+    auto step = [&](const auto& d, bool xfirst) {
+        pair(d, 0, true, acc_j, xfirst);
 #pragma unroll
         for (int a = 0; a < NJ; ++a) acc_j[a] = rot1(acc_j[a]);
     };
@@ -945,9 +961,9 @@ __device__ __forceinline__ void walk_tile(int lane, bool diagonal, T (&acc_j)[NJ
 #pragma unroll 1
         for (int k = 0; k < kTile; k += 2) {
             auto b = load(lane + k + 1);
-            step(a, true);
+            step(a, false);
             a = load(lane + k + 2);             // slot <= 127: inside the doubled block
-            step(b, true);
+            step(b, false);
         }
     } else {
         // pairs (l, l + k) for k = 1..31, and k = 32 for lanes 0..31 only
@@ -955,13 +971,13 @@ __device__ __forceinline__ void walk_tile(int lane, bool diagonal, T (&acc_j)[NJ
 #pragma unroll 1
         for (int k = 1; k < kTile / 2 - 1; k += 2) {
             auto b = load(lane + k + 1);
-            step(a, true);
+            step(a, energy_xfirst(true, 1));    // k odd, below kTile / 2 - 1
             a = load(lane + k + 2);
-            step(b, true);
+            step(b, energy_xfirst(true, 2));
         }
         auto b = load(lane + kTile / 2);
-        step(a, true);
-        pair(b, 0, lane < kTile / 2, acc_j);
+        step(a, false);
+        pair(b, 0, lane < kTile / 2, acc_j, false);
         // lane l now holds j = l + 32; j = l sits in lane (l - 32) mod 64
 #pragma unroll
         for (int a = 0; a < NJ; ++a) acc_j[a] = from_lane(acc_j[a], (lane + kTile / 2) & (kTile - 1));
@@ -976,8 +992,8 @@ __device__ __forceinline__ void walk_tile_rows2(int lane, T (&acc_j)[NJ], Load&&
 #pragma unroll
     for (int a = 0; a < NJ; ++a) acc_j[a] = T(0);
     auto step = [&](const auto& d) {
-        pair(d, 0, true, acc_j);
-        pair(d, 1, true, acc_j);
+        pair(d, 0, true, acc_j, false);
+        pair(d, 1, true, acc_j, false);
 #pragma unroll
         for (int a = 0; a < NJ; ++a) acc_j[a] = rot1(acc_j[a]);
     };
@@ -1308,15 +1324,15 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
             ai[r] += act ? hij : T(0);
             acc[0] += act ? hji : T(0);
         };
-        auto pair = [&](const JD& d, int r, bool act, T (&acc)[1]) {
+        auto pair = [&](const JD& d, int r, bool act, T (&acc)[1], bool) {
             pair_any(d, r, act, acc, std::false_type{});
         };
-        auto pair_sep = [&](const JD& d, int r, bool act, T (&acc)[1]) {
+        auto pair_sep = [&](const JD& d, int r, bool act, T (&acc)[1], bool) {
             pair_any(d, r, act, acc, std::true_type{});
         };
         if constexpr (CUT) {
             auto pm = [&](auto mode) {
-                return [&, mode](const JD& d, int r, bool act, T (&acc)[1]) {
+                return [&, mode](const JD& d, int r, bool act, T (&acc)[1], bool) {
                     pair_any(d, r, act, acc, mode);
                 };
             };
@@ -1365,7 +1381,7 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
                     if (on) {
                         const JD d = load(jl);
                         const T dx = px - d.p.x, dy = py - d.p.y, dz = pz - d.p.z;
-                        const T r2 = dx * dx + dy * dy + dz * dz;
+                        const T r2 = dist2(dx, dy, dz);
                         const T invr = rsq(r2);
                         const T rr = r2 * invr;
                         siv[lane] = slow_H(rr, invr, prt, d.S);         // H(r; rt_i, S_j)
@@ -1492,6 +1508,107 @@ __global__ void k_radii_finalize(int n_atoms, const T* __restrict__ RHO, GBConst
 // ================================================================ pass 2
 // Coulomb + GB energy, explicit pair forces, G = dE/dR, phi = dE/dq.
 
+// Constants of the energy pass.  Without salt the pair terms take the charges
+// scaled by sqrt(kC), so that qq = kC q_i q_j carries the Coulomb constant and
+// tau = kT / kC the GB factor; the phi and G sums are rescaled when they are
+// rounded (sPhi, sG), which saves four multiplications per pair.  With salt the
+// factors vary per pair and the charges stay as given.
+template <typename T, bool SALT>
+struct EnergyK {
+    T sq, tau, qtau, sPhi, sG;
+    __device__ __forceinline__ EnergyK(T kC, T kT)
+    {
+        sq = SALT ? T(1) : T(sqrt(kC));
+        tau = SALT || kC == T(0) ? T(0) : kT / kC;
+        qtau = T(-0.25) * tau;
+        sPhi = sq;
+        sG = SALT ? T(1) : T(0.5) * tau;
+    }
+};
+
+// Terms of one pair: the force on i is -fr (dx, dy, dz), G_i gains cg R_j, phi_i
+// the weight below times q_j, E_C qq / r and E_GB qq (kd) / f.
+template <typename T>
+struct EnergyTerms {
+    T dx, dy, dz, invr, invf, qq, kd, fr, cg;
+    bool act;
+};
+
+template <typename T, bool GRAD, bool SALT, bool CUT>
+__device__ __forceinline__ EnergyTerms<T> energy_terms(T xi, T yi, T zi, T qi, T Ri, T ai, T xj, T yj,
+                                                       T zj, T qj, T Rj, T aj, bool act, bool xfirst,
+                                                       T kC, T kT, const EnergyK<T, SALT>& ek,
+                                                       const SaltK<T>& sk, T cE2)
+{
+    EnergyTerms<T> e;
+    e.dx = xi - xj; e.dy = yi - yj; e.dz = zi - zj;
+    const T u = xfirst ? e.dx : e.dy, v = xfirst ? e.dy : e.dx;
+    const T r2 = fma(e.dz, e.dz, fma(v, v, u * u));
+    if constexpr (CUT) act = act && r2 < cE2;            // pairs beyond the cutoff drop out
+    e.act = act;
+    e.invr = rsq(r2);
+    T t = r2 * (ai * aj);                // r^2 log2(e) / (4 R_i R_j)
+    T ex = exp2neg(t);                   // exp(-D)
+    T f2 = Ri * Rj * ex + r2;
+    e.invf = rsq(f2);
+    e.qq = act ? qi * qj : T(0);
+    // GB factor of the pair: with salt kd = k (1/eps_in -
+    // exp(-kappa f)/eps_out) and the slope factor ks = kd - k kappa f
+    // exp(-kappa f)/eps_out (d/df (kd/f) = -ks/f^2); without salt both
+    // are kT = k (1/eps_in - 1/eps_out) = tau kC, carried by the scaled
+    // charges and tau
+    e.kd = kT;
+    [[maybe_unused]] T ks = kT;
+    if constexpr (SALT) {
+        const T f = f2 * e.invf;
+        const T es = sk.kO * exp2neg(sk.kap2 * f);
+        e.kd = kC - es;
+        ks = e.kd - es * sk.kap * f;
+    }
+    if constexpr (GRAD) {
+        T invf3 = e.invf * e.invf * e.invf;
+        T invr3 = e.invr * e.invr * e.invr;
+        if constexpr (SALT) {
+            e.fr = e.qq * (ks * invf3 * (T(1) - T(0.25) * ex) - kC * invr3);   // (dE/dr)/r
+            e.cg = T(0.5) * ks * e.qq * invf3 * ex * (T(1) + t * T(kLn2));
+        } else {
+            // scaled charges: G term over tau / 2
+            e.fr = e.qq * ((ex * ek.qtau + ek.tau) * invf3 - invr3);
+            e.cg = e.qq * invf3 * ex * (T(1) + t * T(kLn2));
+        }
+    }
+    return e;
+}
+
+// The phi weight of a pair (scaled charges: over sqrt(kC)).
+template <typename T, bool SALT>
+__device__ __forceinline__ T energy_weight(T invr, T invf, T kC, T kd, const EnergyK<T, SALT>& ek)
+{
+    if constexpr (SALT) return kC * invr - kd * invf;
+    return invr - ek.tau * invf;
+}
+
+// Self terms (f_ii = R_i): -(kd/2) q_i^2 / R_i in E_GB, -kd q_i / R_i in phi,
+// (ks/2) q_i^2 / R_i^2 in G (without salt in the scaled form of the walk's sums).
+template <typename T, bool SALT>
+__device__ __forceinline__ void energy_self(T qi, T Ri, T kC, const EnergyK<T, SALT>& ek,
+                                            const SaltK<T>& sk, T& eG, T& phii, T& Gi)
+{
+    const T invR = rcp(Ri);
+    if constexpr (SALT) {
+        const T es = sk.kO * exp2neg(sk.kap2 * Ri);
+        const T kd = kC - es;
+        const T ks = kd - es * sk.kap * Ri;
+        eG += T(0.5) * qi * qi * kd * invR;
+        phii -= kd * qi * invR;
+        Gi += T(0.5) * ks * qi * qi * invR * invR;
+    } else {
+        eG += T(0.5) * qi * qi * invR;
+        phii -= ek.tau * qi * invR;
+        Gi += qi * qi * invR * invR;
+    }
+}
+
 // One work item of R (1 or 2) i blocks; see radii_item.
 template <typename T, bool GRAD, int R, bool SALT, bool CUT, bool ONE>
 __device__ __forceinline__ void energy_item(const WorkItem& w, int lane, Q4<T>* sj, T* sR, T* sA,
@@ -1501,15 +1618,8 @@ __device__ __forceinline__ void energy_item(const WorkItem& w, int lane, Q4<T>* 
                                             const Work<T>& wk, unsigned long long tmask)
 {
     constexpr int NJ = GRAD ? 5 : 1;
-    // Without salt the pair terms take the charges scaled by sqrt(kC), so that
-    // qq = kC q_i q_j carries the Coulomb constant and tau = kT / kC the GB
-    // factor; the phi and G sums are rescaled when they are rounded (sPhi,
-    // sG), which saves four multiplications per pair.  With salt the factors
-    // vary per pair and the charges stay as given.
-    const T sq = SALT ? T(1) : T(sqrt(kC));
-    const T tau = SALT || kC == T(0) ? T(0) : kT / kC;
-    const T qtau = T(-0.25) * tau;
-    const T sPhi = sq, sG = SALT ? T(1) : T(0.5) * tau;
+    const EnergyK<T, SALT> ek(kC, kT);
+    const T sq = ek.sq, tau = ek.tau, sPhi = ek.sPhi, sG = ek.sG;
     T xi[R], yi[R], zi[R], qi[R], Ri[R], ai[R];
     bool vi[R];
 #pragma unroll
@@ -1586,88 +1696,34 @@ __device__ __forceinline__ void energy_item(const WorkItem& w, int lane, Q4<T>* 
             const int m = s & (kTile - 1);
             return JD{sj[m], sR[m], sA[m]};
         };
-        auto pair = [&](const JD& d, int r, bool act, T (&acc)[NJ]) {
+        auto pair = [&](const JD& d, int r, bool act, T (&acc)[NJ], bool xfirst) {
             const Q4<T>& p = d.p;
-            const T rj = d.Rv;
-            T dx = xi[r] - p.x, dy = yi[r] - p.y, dz = zi[r] - p.z;
-            T r2 = dx * dx + dy * dy + dz * dz;
-            if constexpr (CUT) act = act && r2 < ck.cE2;     // pairs beyond the cutoff drop out
-            T invr = rsq(r2);
-            T t = r2 * (ai[r] * d.Av);            // r^2 log2(e) / (4 R_i R_j)
-            T ex = exp2neg(t);                   // exp(-D)
-            T f2 = Ri[r] * rj * ex + r2;
-            T invf = rsq(f2);
-            T qq = act ? qi[r] * p.w : T(0);
-            eC[r] += qq * invr;
-            // GB factor of the pair: with salt kd = k (1/eps_in -
-            // exp(-kappa f)/eps_out) and the slope factor ks = kd - k kappa f
-            // exp(-kappa f)/eps_out (d/df (kd/f) = -ks/f^2); without salt both
-            // are kT = k (1/eps_in - 1/eps_out) = tau kC, carried by the scaled
-            // charges and tau
-            [[maybe_unused]] T kd = kT, ks = kT;
-            if constexpr (SALT) {
-                const T f = f2 * invf;
-                const T es = sk.kO * exp2neg(sk.kap2 * f);
-                kd = kC - es;
-                ks = kd - es * sk.kap * f;
-                eG[r] += qq * kd * invf;
-            } else {
-                eG[r] += qq * invf;
-            }
+            const EnergyTerms<T> e = energy_terms<T, GRAD, SALT, CUT>(
+                xi[r], yi[r], zi[r], qi[r], Ri[r], ai[r], p.x, p.y, p.z, p.w, d.Rv, d.Av, act, xfirst, kC, kT,
+                ek, sk, ck.cE2);
+            eC[r] = fma(e.qq, e.invr, eC[r]);
+            eG[r] = fma(SALT ? e.qq * e.kd : e.qq, e.invf, eG[r]);
             if constexpr (GRAD) {
-                T qj = act ? p.w : T(0);
-                T qi_ = act ? qi[r] : T(0);
-                T invf3 = invf * invf * invf;
-                T invr3 = invr * invr * invr;
-                T wgt, fr, cg;
-                if constexpr (SALT) {
-                    wgt = kC * invr - kd * invf;
-                    fr = qq * (ks * invf3 * (T(1) - T(0.25) * ex) - kC * invr3);   // (dE/dr)/r
-                    cg = T(0.5) * ks * qq * invf3 * ex * (T(1) + t * T(kLn2));
-                } else {
-                    // scaled charges: phi weight over sqrt(kC), G term over tau / 2
-                    wgt = invr - tau * invf;
-                    fr = qq * ((ex * qtau + tau) * invf3 - invr3);
-                    cg = qq * invf3 * ex * (T(1) + t * T(kLn2));
-                }
-                phii[r] += wgt * qj;
-                T fx = fr * dx, fy = fr * dy, fz = fr * dz;
-                fxi[r] -= fx; fyi[r] -= fy; fzi[r] -= fz;
-                Gi[r] += cg * rj;
-                acc[0] += fx;
-                acc[1] += fy;
-                acc[2] += fz;
-                acc[3] += cg * Ri[r];
-                acc[4] += wgt * qi_;
+                const T qj = e.act ? p.w : T(0);
+                const T qi_ = e.act ? qi[r] : T(0);
+                const T wgt = energy_weight<T, SALT>(e.invr, e.invf, kC, e.kd, ek);
+                phii[r] = fma(wgt, qj, phii[r]);
+                fxi[r] = fma(-e.fr, e.dx, fxi[r]);
+                fyi[r] = fma(-e.fr, e.dy, fyi[r]);
+                fzi[r] = fma(-e.fr, e.dz, fzi[r]);
+                Gi[r] = fma(e.cg, d.Rv, Gi[r]);
+                acc[0] = fma(e.fr, e.dx, acc[0]);
+                acc[1] = fma(e.fr, e.dy, acc[1]);
+                acc[2] = fma(e.fr, e.dz, acc[2]);
+                acc[3] = fma(e.cg, Ri[r], acc[3]);
+                acc[4] = fma(wgt, qi_, acc[4]);
             }
         };
         if constexpr (R == 1)
             walk_tile<T, NJ>(lane, J == w.I, aj, load, pair);
         else
             walk_tile_rows2<T, NJ>(lane, aj, load, pair);
-        if (R == 1 && J == w.I) {
-            // self terms (f_ii = R_i): -(kd/2) q_i^2 / R_i in E_GB, -kd q_i / R_i
-            // in phi, (ks/2) q_i^2 / R_i^2 in G (without salt in the scaled
-            // form of the walk's sums)
-            T invR = rcp(Ri[0]);
-            [[maybe_unused]] T kd = kT, ks = kT;
-            if constexpr (SALT) {
-                const T es = sk.kO * exp2neg(sk.kap2 * Ri[0]);
-                kd = kC - es;
-                ks = kd - es * sk.kap * Ri[0];
-                eG[0] += T(0.5) * qi[0] * qi[0] * kd * invR;
-                if constexpr (GRAD) {
-                    phii[0] -= kd * qi[0] * invR;
-                    Gi[0] += T(0.5) * ks * qi[0] * qi[0] * invR * invR;
-                }
-            } else {
-                eG[0] += T(0.5) * qi[0] * qi[0] * invR;
-                if constexpr (GRAD) {
-                    phii[0] -= tau * qi[0] * invR;
-                    Gi[0] += qi[0] * qi[0] * invR * invR;
-                }
-            }
-        }
+        if (R == 1 && J == w.I) energy_self<T, SALT>(qi[0], Ri[0], kC, ek, sk, eG[0], phii[0], Gi[0]);
         if constexpr (GRAD) {
             const int g = w.base + clamp_atom(j, w.n);
             long long v[5];
@@ -1854,6 +1910,24 @@ __device__ __forceinline__ T brt_from(unsigned long long gfx, double dRdPsi, T r
     return (T)(B * (double)rt);
 }
 
+// Terms of one overlapping pair in closed form: what joins the i side's sums
+// (iv: three force components, dE/drho) and the j side's (jv).
+template <typename T>
+__device__ __forceinline__ void chain_deferred(T r, T invr, T dx, T dy, T dz, T rti, T Si, T bi, T si,
+                                               T rtj, T Sj, T bj, T sj, T* iv, T* jv)
+{
+    T ga[3], gb[3];
+    slow_grad(r, invr, rti, Sj, ga);            // H(r; rt_i, S_j)
+    slow_grad(r, invr, rtj, Si, gb);            // H(r; rt_j, S_i)
+    // dE/dr = bi dH_ij/dr + bj dH_ji/dr
+    const T fr = T(fma(bi, ga[0], bj * gb[0])) * invr;
+    const T fx = fr * dx, fy = fr * dy, fz = fr * dz;
+    iv[0] = -fx; iv[1] = -fy; iv[2] = -fz;
+    iv[3] = T(fma(bi, ga[1], si * bj * gb[2]));
+    jv[0] = fx; jv[1] = fy; jv[2] = fz;
+    jv[3] = T(fma(sj * bi, ga[2], bj * gb[1]));
+}
+
 template <typename T, int R, bool CUT, bool ONE>
 __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* sj, Q4<T>* sb,
                                            unsigned long long* sdef, int* slist,
@@ -1960,7 +2034,7 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
             const Q4<T>& p = d.p;
             const Q4<T>& b = d.b;
             T dx = xi[r] - p.x, dy = yi[r] - p.y, dz = zi[r] - p.z;
-            T r2 = dx * dx + dy * dy + dz * dz;
+            T r2 = dist2(dx, dy, dz);
             T invr = rsq(r2);
             T rr = r2 * invr;
             const T bj_ = act ? b.y : T(0);
@@ -1985,24 +2059,25 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
                 chain_pair(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, dEdr, gij2, gji2,
                            dri[r], acc[3]);
             }
-            T fr = dEdr * invr;
-            T fx = fr * dx, fy = fr * dy, fz = fr * dz;
-            fxi[r] -= fx; fyi[r] -= fy; fzi[r] -= fz;
-            dri[r] += si[r] * bj_ * gji2;
-            acc[0] += fx;
-            acc[1] += fy;
-            acc[2] += fz;
-            acc[3] += b.z * bi_ * gij2;
+            const T fr = dEdr * invr;
+            fxi[r] = fma(-fr, dx, fxi[r]);
+            fyi[r] = fma(-fr, dy, fyi[r]);
+            fzi[r] = fma(-fr, dz, fzi[r]);
+            dri[r] = fma(si[r] * bj_, gji2, dri[r]);
+            acc[0] = fma(fr, dx, acc[0]);
+            acc[1] = fma(fr, dy, acc[1]);
+            acc[2] = fma(fr, dz, acc[2]);
+            acc[3] = fma(b.z * bi_, gij2, acc[3]);
         };
-        auto pair = [&](const JD& d, int r, bool act, T (&acc)[4]) {
+        auto pair = [&](const JD& d, int r, bool act, T (&acc)[4], bool) {
             pair_any(d, r, act, acc, std::false_type{});
         };
-        auto pair_sep = [&](const JD& d, int r, bool act, T (&acc)[4]) {
+        auto pair_sep = [&](const JD& d, int r, bool act, T (&acc)[4], bool) {
             pair_any(d, r, act, acc, std::true_type{});
         };
         if constexpr (CUT) {
             auto pm = [&](auto mode) {
-                return [&, mode](const JD& d, int r, bool act, T (&acc)[4]) {
+                return [&, mode](const JD& d, int r, bool act, T (&acc)[4], bool) {
                     pair_any(d, r, act, acc, mode);
                 };
             };
@@ -2091,18 +2166,13 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
                         const Q4<T>& p = d.p;
                         const Q4<T>& b = d.b;
                         const T dx = px - p.x, dy = py - p.y, dz = pz - p.z;
-                        const T r2 = dx * dx + dy * dy + dz * dz;
+                        const T r2 = dist2(dx, dy, dz);
                         const T invr = rsq(r2);
                         const T rr = r2 * invr;
-                        T ga[3], gb[3];
-                        slow_grad(rr, invr, prt, b.x, ga);              // H(r; rt_i, S_j)
-                        slow_grad(rr, invr, p.w, pS, gb);               // H(r; rt_j, S_i)
-                        const T bj_ = b.y;
-                        // dE/dr = bi dH_ij/dr + bj dH_ji/dr
-                        const T fr = T(fma(bi_, ga[0], bj_ * gb[0])) * invr;
-                        const T fx = fr * dx, fy = fr * dy, fz = fr * dz;
-                        siv[lane] = Q4<T>{-fx, -fy, -fz, T(fma(bi_, ga[1], ps * bj_ * gb[2]))};
-                        const T jv[4] = {fx, fy, fz, T(fma(b.z * bi_, ga[2], bj_ * gb[1]))};
+                        T iv[4], jv[4];
+                        chain_deferred(rr, invr, dx, dy, dz, prt, pS, bi_, ps, p.w, b.x, b.y, b.z, iv,
+                                       jv);
+                        siv[lane] = Q4<T>{iv[0], iv[1], iv[2], iv[3]};
 #pragma unroll
                         for (int a = 0; a < 4; ++a)
                             atomicAdd(&sdef[a * kTile + jl],
@@ -2202,6 +2272,8 @@ __global__ __launch_bounds__(kTile * W) void k_chain_pairs(
     }
 }
 
+
+#include "gbmc_wide.h"
 
 // ===================================================== one queued launch
 // The pair passes of one call (descreening, energy / explicit forces, Born
@@ -2945,8 +3017,7 @@ static inline int cut_groups(int cap, int W)
 }
 
 template <typename T>
-hipError_t launch_radii(const WorkItem* items, int n_items, int wpg, int n_atoms,
-                        const CutPlan& cp,
+hipError_t launch_radii(const PassShape& pr, int n_atoms, const CutPlan& cp,
                         const T* x, const T* y, const T* z, const T* rho, const T* screen,
                         const GBConst& c, const Work<T>& w, T* born_R, hipStream_t s,
                         hipEvent_t* ev, const T* q)
@@ -2964,17 +3035,22 @@ hipError_t launch_radii(const WorkItem* items, int n_items, int wpg, int n_atoms
                        cp.n_blocks, n_atoms, w.perm, x, y, z, q, rho, screen,
                        (T)c.offset, w.P, w.Gx, w.box, zc);
     if (c.rgbmax > 0.0 || c.cutoff > 0.0) launch_cut_lists<T>(cp, c, w, s);
-    if (n_items > 0) {
+    if (pr.n_items > 0) {
         if (c.rgbmax > 0.0)
-            GBMC_DISPATCH_W(wpg, GBMC_LAUNCH_TIMED(ev, kKRadii, (k_radii_pairs<T, W, true>),
-                                                   dim3(cut_groups(w.cut_cap, W)), dim3(kTile * W),
-                                                   s, items, n_items, w.citems[0], w.ccount, w.P,
-                                                   w.Gx, w.I_fx, w.ovf, (T)c.rgbmax, w.box))
+            GBMC_DISPATCH_W(pr.waves_per_group,
+                            GBMC_LAUNCH_TIMED(ev, kKRadii, (k_radii_pairs<T, W, true>),
+                                              dim3(cut_groups(w.cut_cap, W)), dim3(kTile * W), s,
+                                              pr.items, pr.n_items, w.citems[0], w.ccount, w.P, w.Gx,
+                                              w.I_fx, w.ovf, (T)c.rgbmax, w.box))
+        else if (pr.wide)
+            GBMC_LAUNCH_TIMED(ev, kKRadii, k_radii_wide<T>, dim3(pr.n_items), dim3(kWide * kTile), s,
+                              pr.items, w.P, w.Gx, w.I_fx, w.ovf, w.box);
         else
-            GBMC_DISPATCH_W(wpg, GBMC_LAUNCH_TIMED(ev, kKRadii, (k_radii_pairs<T, W, false>),
-                                                   dim3(blocks_for(n_items, W)), dim3(kTile * W), s,
-                                                   items, n_items, w.citems[0], w.ccount, w.P,
-                                                   w.Gx, w.I_fx, w.ovf, (T)0, w.box))
+            GBMC_DISPATCH_W(pr.waves_per_group,
+                            GBMC_LAUNCH_TIMED(ev, kKRadii, (k_radii_pairs<T, W, false>),
+                                              dim3(blocks_for(pr.n_items, W)), dim3(kTile * W), s,
+                                              pr.items, pr.n_items, w.citems[0], w.ccount, w.P, w.Gx,
+                                              w.I_fx, w.ovf, (T)0, w.box))
     }
     hipLaunchKernelGGL(k_radii_finalize<T>, dim3(blocks_for(n_atoms, 256)), dim3(256), 0, s, n_atoms,
                        rho, c, w, born_R);
@@ -3016,8 +3092,19 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
                                       dim3(kTile * W), s,                                        \
                                       pe.items, pe.n_items, w.P, w.R_t, w.a_t, (T)c.kC, (T)c.kT, \
                                       sk, ck, w))
+#define GBMC_ENERGY_WIDE(G_, S_)                                                                 \
+    GBMC_LAUNCH_TIMED(ev, kKEnergy, (k_energy_wide<T, G_, S_>), dim3(pe.n_items),                   \
+                      dim3(kWideEnergy * kTile), s, pe.items, w.P, (T)c.kC, (T)c.kT, sk, w)
         const bool salt = c.kappa != 0.0, cut = c.cutoff > 0.0, one = pe.one_tile;
-        if (grad) {
+        if (pe.wide && !cut) {
+            if (grad) {
+                if (salt) GBMC_ENERGY_WIDE(true, true);
+                else GBMC_ENERGY_WIDE(true, false);
+            } else {
+                if (salt) GBMC_ENERGY_WIDE(false, true);
+                else GBMC_ENERGY_WIDE(false, false);
+            }
+        } else if (grad) {
             if (salt) {
                 if (cut) GBMC_ENERGY_LAUNCH(true, true, true, false)
                 else if (one) GBMC_ENERGY_LAUNCH(true, true, false, true)
@@ -3039,6 +3126,7 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
             }
         }
 #undef GBMC_ENERGY_LAUNCH
+#undef GBMC_ENERGY_WIDE
     }
     const int n_sum = (e_coul || e_gb) ? n_sums : 0;
     const int n_fin = grad ? blocks_for(n_atoms, 256) : 0;
@@ -3055,6 +3143,9 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
                                               dim3(cut_groups(w.cut_cap, W)), dim3(kTile * W), s,
                                               pc.items, pc.n_items, w.P, w.Gx, w,
                                               (T)c.rgbmax))
+        else if (pc.wide)
+            GBMC_LAUNCH_TIMED(ev, kKChain, k_chain_wide<T>, dim3(pc.n_items), dim3(kWide * kTile), s,
+                              pc.items, w.P, w.Gx, w);
         else if (pc.one_tile)
             GBMC_DISPATCH_W(pc.waves_per_group,
                             GBMC_LAUNCH_TIMED(ev, kKChain, (k_chain_pairs<T, W, false, true>),
@@ -3210,7 +3301,7 @@ hipError_t launch_remd_exchange(int M, const double* E_rung, const int32_t* Ne, 
 }
 
 #define GBMC_INSTANTIATE(T)                                                                      \
-    template hipError_t launch_radii<T>(const WorkItem*, int, int, int, const CutPlan&,         \
+    template hipError_t launch_radii<T>(const PassShape&, int, const CutPlan&,                  \
                                         const T*,                                                \
                                         const T*, const T*, const T*, const T*, const GBConst&,  \
                                         const Work<T>&, T*, hipStream_t, hipEvent_t*,            \
