@@ -317,9 +317,11 @@ gbmc_status gbmc_sites_create(gbmc_plan* plan, gbmc_sites** sites, int32_t n_sit
                               const double* state_gref, const int32_t* state_count);
 void gbmc_sites_destroy(gbmc_sites* sites);
 int32_t gbmc_sites_n_candidates(const gbmc_sites* sites);
-/* Bytes of caller-owned device workspace mc_state_dE and mc_step need: the
- * site atoms' FP64 potentials as int64 fixed point (2^-44 kcal/mol/e), which
- * mc_state_dE clears and fills on every call. */
+/* Bytes of caller-owned device workspace mc_state_dE, mc_step and mc_sweep need:
+ * the site atoms' FP64 potentials as int64 fixed point (2^-44 kcal/mol/e), which
+ * mc_state_dE and mc_sweep clear and fill on every call, and (where mc_sweep
+ * supports the sites) a double for every two sites of a system, which mc_sweep
+ * fills with their couplings. */
 size_t gbmc_sites_workspace_bytes(const gbmc_sites* sites);
 
 /* Delta E_elec and Delta G of every candidate state change (sections II.A-B):

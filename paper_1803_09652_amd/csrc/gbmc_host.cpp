@@ -119,6 +119,8 @@ struct gbmc_sites {
     size_t n_site_atoms = 0;         // fixed-point potential slots in the site workspace
     int32_t max_sys_site_atoms = 0;  // largest number of site atoms in one system
     int32_t max_sys_sites = 0;       // largest number of sites of one kind in one system
+    int32_t max_all_sites = 0;       // largest number of sites in one system
+    int64_t n_couple = 0;            // couplings of the sequential sweep (0: not supported)
     void* d_mem = nullptr;
     SiteDev dev{};
 };
@@ -1108,6 +1110,27 @@ gbmc_status gbmc_sites_create(gbmc_plan* p, gbmc_sites** out, int32_t n_sites,
                     rows.push_back(r);
                 }
         }
+        // the sequential sweep: pairs of sites, and the offsets of each system's
+        // couplings (none where a system exceeds the sweep's limits)
+        std::vector<int32_t> sys_site(B + 1, 0), couples;
+        std::vector<int64_t> couple_off(B + 1, 0);
+        bool sweep_ok = true;
+        for (int32_t b = 0; b < B; ++b) {
+            const int32_t s0 = first[b] >= 0 ? first[b] : sys_site[b];
+            sys_site[b] = s0;
+            sys_site[b + 1] = first[b] >= 0 ? last[b] + 1 : s0;
+            sweep_ok = sweep_ok && sys_sa[b + 1] - sys_sa[b] <= kMaxSweepSiteAtoms;
+        }
+        for (int32_t b = 0; sweep_ok && b < B; ++b) {
+            const int32_t n = sys_site[b + 1] - sys_site[b];
+            couple_off[b + 1] = couple_off[b] + (int64_t)n * n;
+            for (int32_t i = sys_site[b]; i < sys_site[b + 1]; ++i)
+                for (int32_t j = i; j < sys_site[b + 1]; ++j) {
+                    couples.push_back(i);
+                    couples.push_back(j);
+                }
+        }
+        if (couples.size() / 2 > 0x7fffffff) return fail(GBMC_ERR_UNSUPPORTED, "too many pairs of sites");
         // one device allocation for every table
         size_t o = 0;
         auto seg = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
@@ -1116,7 +1139,8 @@ gbmc_status gbmc_sites_create(gbmc_plan* p, gbmc_sites** out, int32_t n_sites,
                o_gref = seg(8 * n_st), o_cnt = seg(4 * n_st), o_cand = seg(4 * (S + 1)),
                o_po = seg(4 * (B + 1)), o_ps = seg(4 * prot.size()), o_ro = seg(4 * (B + 1)),
                o_rs = seg(4 * redox.size()), o_syssa = seg(4 * (B + 1)),
-               o_rows = seg(sizeof(RowItem) * rows.size());
+               o_rows = seg(sizeof(RowItem) * rows.size()), o_ss = seg(4 * (B + 1)),
+               o_co = seg(8 * (B + 1)), o_cp = seg(4 * couples.size());
         std::vector<char> h(o, 0);
         auto put = [&](size_t at, const void* src, size_t bytes) { if (bytes) std::memcpy(h.data() + at, src, bytes); };
         if (S > 0) {
@@ -1137,14 +1161,19 @@ gbmc_status gbmc_sites_create(gbmc_plan* p, gbmc_sites** out, int32_t n_sites,
         put(o_rs, redox.data(), 4 * redox.size());
         put(o_syssa, sys_sa.data(), 4 * (B + 1));
         put(o_rows, rows.data(), sizeof(RowItem) * rows.size());
+        put(o_ss, sys_site.data(), 4 * (B + 1));
+        put(o_co, couple_off.data(), 8 * (B + 1));
+        put(o_cp, couples.data(), 4 * couples.size());
         auto* sp = new gbmc_sites();
         sp->plan = p;
         sp->n_sites = S;
         sp->n_cand = cand[S];
         sp->n_rowitems = (int32_t)rows.size();
         sp->n_site_atoms = (size_t)n_sa;
+        sp->n_couple = couple_off[B];
         for (int32_t b = 0; b < B; ++b) {
             sp->max_sys_site_atoms = std::max(sp->max_sys_site_atoms, sys_sa[b + 1] - sys_sa[b]);
+            sp->max_all_sites = std::max(sp->max_all_sites, sys_site[b + 1] - sys_site[b]);
             sp->max_sys_sites = std::max({sp->max_sys_sites, prot_off[b + 1] - prot_off[b],
                                           redox_off[b + 1] - redox_off[b]});
         }
@@ -1175,6 +1204,10 @@ gbmc_status gbmc_sites_create(gbmc_plan* p, gbmc_sites** out, int32_t n_sites,
         sd.site_sa_offset = sd.site_atom_offset;
         sd.sys_sa_offset = (const int32_t*)(d + o_syssa);
         sd.rowitems = (const RowItem*)(d + o_rows);
+        sd.n_couples = (int32_t)(couples.size() / 2);
+        sd.couples = (const int32_t*)(d + o_cp);
+        sd.sys_site_offset = (const int32_t*)(d + o_ss);
+        sd.sys_couple_offset = (const int64_t*)(d + o_co);
         *out = sp;
         return GBMC_OK;
     } catch (const std::bad_alloc&) {
@@ -1193,7 +1226,7 @@ int32_t gbmc_sites_n_candidates(const gbmc_sites* s) { return s ? s->n_cand : 0;
 
 size_t gbmc_sites_workspace_bytes(const gbmc_sites* s)
 {
-    return s ? align256(std::max<size_t>(8 * s->n_site_atoms, 8)) : 0;
+    return s ? align256(std::max<size_t>(8 * (s->n_site_atoms + (size_t)s->n_couple), 8)) : 0;
 }
 
 static gbmc_status check_sites(const gbmc_plan* p, const gbmc_sites* s, const void* sws)
@@ -1281,16 +1314,16 @@ gbmc_status mc_sweep(gbmc_plan* p, const gbmc_sites* s, const gbmc_atoms* a, voi
     GBConst c = make_const(gp);
     hipError_t e;
     if (p->prec == GBMC_FP32_FIXED)
-        e = launch_mc_sweep<float>(s->dev, p->n_sys, s->max_sys_site_atoms, (const float*)a->x,
+        e = launch_mc_sweep<float>(s->dev, p->n_sys, s->max_all_sites, (const float*)a->x,
                                    (const float*)a->y, (const float*)a->z, (const float*)a->q,
                                    (float*)q, c, carve<float>(p, ws), (unsigned long long*)sws,
-                                   current_state, pH, E_volt, T, kinds, u, n_electrons, counters,
+                                   (double*)sws + s->n_site_atoms, current_state, pH, E_volt, T, kinds, u, n_electrons, counters,
                                    accepted, dG, stream);
     else
-        e = launch_mc_sweep<double>(s->dev, p->n_sys, s->max_sys_site_atoms, (const double*)a->x,
+        e = launch_mc_sweep<double>(s->dev, p->n_sys, s->max_all_sites, (const double*)a->x,
                                     (const double*)a->y, (const double*)a->z, (const double*)a->q,
                                     (double*)q, c, carve<double>(p, ws), (unsigned long long*)sws,
-                                    current_state, pH, E_volt, T, kinds, u, n_electrons, counters,
+                                    (double*)sws + s->n_site_atoms, current_state, pH, E_volt, T, kinds, u, n_electrons, counters,
                                     accepted, dG, stream);
     return e == hipSuccess ? GBMC_OK : hip_fail(e, "mc_sweep launch");
 }

@@ -164,6 +164,12 @@ struct SiteDev {
     const int32_t* site_sa_offset;    // [S+1]: first flattened site-atom slot of each site
     const int32_t* sys_sa_offset;     // [B+1]
     const RowItem* rowitems;
+    // the sequential sweep: the pairs of sites (m <= m') of every system, and where
+    // a system's S x S couplings start
+    int32_t n_couples;
+    const int32_t* couples;           // [2 n_couples]
+    const int32_t* sys_site_offset;   // [B+1]
+    const int64_t* sys_couple_offset; // [B]
 };
 
 struct GBConst {
@@ -261,12 +267,12 @@ hipError_t launch_mc_step(const SiteDev& sd, int n_sys, const T* x, const T* y, 
                           int32_t* n_electrons, int64_t* counters, int32_t* accepted,
                           hipStream_t s, hipEvent_t* ev);
 template <typename T>
-hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int n_sa_max, const T* x, const T* y,
+hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, const T* x, const T* y,
                            const T* z, const T* q, T* q_out, const GBConst& c, const Work<T>& w,
-                           unsigned long long* phi_fx, int32_t* current_state, const double* pH,
-                           const double* E_volt, double T_kelvin, int kinds, const double* u,
-                           int32_t* n_electrons, int64_t* counters, int32_t* accepted, double* dG,
-                           hipStream_t s);
+                           unsigned long long* phi_fx, double* couple, int32_t* current_state,
+                           const double* pH, const double* E_volt, double T_kelvin, int kinds,
+                           const double* u, int32_t* n_electrons, int64_t* counters,
+                           int32_t* accepted, double* dG, hipStream_t s);
 template <typename T>
 hipError_t launch_md_langevin(int n, T* x, T* y, T* z, T* v, const T* force, const T* inv_mass,
                               const T* xi, const T* xref, double k_restr, double dt, double gamma,

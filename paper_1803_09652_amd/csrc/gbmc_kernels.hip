@@ -2607,7 +2607,6 @@ constexpr int kMC = 256;    // threads of the per-system Monte Carlo step
 // atom pairs is short, and a small workgroup finds room on the CUs beside the
 // force passes sooner than one of 16 waves: 7 us shorter E-REMD step)
 constexpr int kSDE = 256;
-constexpr int kSweep = 1024;  // threads of the per-system sweep kernel (16 waves on one CU)
 
 template <typename T>
 __global__ __launch_bounds__(kSDE) void k_site_dE(
@@ -2800,45 +2799,136 @@ __global__ __launch_bounds__(kMC) void k_mc_step(
     }
 }
 
-// Sequential sweep (section III.A.2): one workgroup per system visits every
-// site of the requested kinds once, protonation sites first, each kind in the
-// order of ascending u[3m] (ties by site index).  The FP64 potentials of all
-// the system's site atoms live in LDS (dynamic, [6][n_sa]: x, y, z, R, A,
-// phi); a visit computes Delta E = dq . phi + 1/2 dq . K_SS . dq from them,
-// and an accepted change adds K dq to every site atom's potential, so the
-// next visit sees the charges it left.  All threads evaluate the same
-// block-reduced Delta G and so take the same decision.
+// Sequential sweep (section III.A.2).  Every site of the requested kinds is
+// visited once, so its proposed change dq (from its state before the sweep and
+// its own uniform) is known before the first visit, and Delta E of a visit is
+//   dq . phi + 1/2 dq . K . dq + sum over the sites m' accepted before it of dq . K . dq',
+// phi at the charges before the sweep.  k_site_couple computes all of these
+// numbers for all pairs of sites at once, spread over the chip, and k_mc_sweep
+// takes the decisions in order from them.  (One workgroup per system that
+// formed each visit's terms in turn, and added K dq to every site atom's
+// potential after each acceptance, was a chain of dependent loads, block
+// reductions and rows of FP64 pair terms on one CU: 158 us on 16 systems of 356
+// site atoms, against 26 us for the two kernels.)
+
+// The state a sweep proposes for site m.
+__device__ __forceinline__ int sweep_proposal(const SiteDev& sd, int m, int s, const double* u)
+{
+    const int tp = pick_index(u[3 * (size_t)m + 1], sd.site_state_offset[m + 1] - sd.site_state_offset[m] - 1);
+    return tp < s ? tp : tp + 1;
+}
+
+constexpr int kCouple = 512;    // threads per pair of sites
+
+// couple[c_offset + i S + j] = dq_i . K . dq_j for sites i != j of a system of S
+// sites, and on the diagonal dq_i . phi_i + 1/2 dq_i . K . dq_i.
+template <typename T>
+__global__ __launch_bounds__(kCouple) void k_site_couple(
+    SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
+    const T* __restrict__ Q, const double* __restrict__ R64, const double* __restrict__ A64, double kC,
+    double kT, double kO, double kap, double cut2, const unsigned long long* __restrict__ phi_fx,
+    const int32_t* __restrict__ current_state, int kinds, const double* __restrict__ u,
+    double* __restrict__ couple)
+{
+    __shared__ double sx[2][kMaxSiteAtoms], sy[2][kMaxSiteAtoms], sz[2][kMaxSiteAtoms];
+    __shared__ double sR[2][kMaxSiteAtoms], sA[2][kMaxSiteAtoms], sdq[2][kMaxSiteAtoms];
+    __shared__ double red[1][kCouple / kTile];
+    const int t = threadIdx.x;
+    const int m[2] = {sd.couples[2 * blockIdx.x], sd.couples[2 * blockIdx.x + 1]};
+    const bool same = m[0] == m[1];
+    if (!(kinds & (1 << sd.site_kind[m[0]])) || !(kinds & (1 << sd.site_kind[m[1]]))) return;
+    double part[1] = {0.0};
+    // half of the workgroup stages each site
+    const int h = t / (kCouple / 2), a = t % (kCouple / 2);
+    static_assert(kCouple / 2 >= kMaxSiteAtoms, "one staging thread per site atom");
+    int na[2], a0[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        a0[k] = sd.site_atom_offset[m[k]];
+        na[k] = sd.site_atom_offset[m[k] + 1] - a0[k];
+    }
+    if (a < na[h]) {
+        const int s = current_state[m[h]], g0 = sd.site_state_offset[m[h]];
+        const double* qn = sd.state_charges + sd.state_charge_offset[g0 + sweep_proposal(sd, m[h], s, u)];
+        const double* qo = sd.state_charges + sd.state_charge_offset[g0 + s];
+        const int g = sd.site_atoms[a0[h] + a];
+        const double R = R64[g], dq = qn[a] - qo[a];
+        sx[h][a] = X[g]; sy[h][a] = Y[g]; sz[h][a] = Z[g];
+        sR[h][a] = R; sA[h][a] = A64[g];
+        sdq[h][a] = dq;
+        if (same && h == 0) {
+            const double k = gb_kd(R, kC, kT, kO, kap) / R;
+            part[0] = dq * ((double)(long long)phi_fx[a0[0] + a] * (1.0 / kScaleP) - k * (double)Q[g])
+                    - 0.5 * dq * dq * k;
+        }
+    }
+    __syncthreads();
+    // pairs of one site: the strict triangle, folded into rows of W entries (row i
+    // and the row as far from the end)
+    const int n = na[0], W = n - 1 + (n & 1), np = same ? n * (n - 1) / 2 : n * na[1];
+    for (int p = t; p < np; p += kCouple) {
+        int i, j;
+        if (!same) {
+            i = p / na[1];
+            j = p - i * na[1];
+        } else {
+            i = p / W;
+            j = p - i * W;
+            if (j >= n - 1 - i) {
+                j -= n - 1 - i;
+                i = n - 1 - (n & 1) - i;
+            }
+            j += i + 1;
+        }
+        const double K = pairK(sx[0][i] - sx[1][j], sy[0][i] - sy[1][j], sz[0][i] - sz[1][j], sR[0][i],
+                               sA[0][i], sR[1][j], sA[1][j], kC, kT, kO, kap, cut2);
+        part[0] = fma(sdq[0][i] * sdq[1][j], K, part[0]);
+    }
+    block_sum<1, kCouple / kTile>(red, part);
+    if (t == 0) {
+        const int b = sd.site_system[m[0]], s0 = sd.sys_site_offset[b], S = sd.sys_site_offset[b + 1] - s0;
+        double* c = couple + sd.sys_couple_offset[b];
+        const int i = m[0] - s0, j = m[1] - s0;
+        c[(size_t)i * S + j] = part[0];
+        c[(size_t)j * S + i] = part[0];
+    }
+}
+
+constexpr int kSweep = 256;             // threads of the per-system sweep
+constexpr int kSweepCache = 64;         // sites of a system up to which its couplings fit in LDS
+
 template <typename T>
 __global__ __launch_bounds__(kSweep) void k_mc_sweep(
-    SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
-    const T* __restrict__ Q, T* __restrict__ Qout, const double* __restrict__ R64,
-    const double* __restrict__ A64, double kC, double kT, double kO, double kap, double cut2,
-    const unsigned long long* __restrict__ phi_fx, int32_t* __restrict__ current_state,
-    const double* __restrict__ pH, const double* __restrict__ E_volt, double T_kelvin, int kinds,
-    const double* __restrict__ u, int32_t* __restrict__ n_electrons,
-    int64_t* __restrict__ counters, int32_t* __restrict__ accepted, double* __restrict__ dG_out)
+    SiteDev sd, T* __restrict__ Qout, const double* __restrict__ couple,
+    int32_t* __restrict__ current_state, const double* __restrict__ pH,
+    const double* __restrict__ E_volt, double T_kelvin, int kinds, const double* __restrict__ u,
+    int32_t* __restrict__ n_electrons, int64_t* __restrict__ counters,
+    int32_t* __restrict__ accepted, double* __restrict__ dG_out)
 {
-    extern __shared__ double s_sa[];
-    __shared__ double sdq[kMaxSiteAtoms];
+    extern __shared__ double sC[];
+    // per site: Delta G at the charges left so far, its value at the visit, the
+    // acceptance uniform; visiting order, current and proposed state, decision
+    __shared__ double dg[kMaxSweepSites], dg_at[kMaxSweepSites], su[kMaxSweepSites];
     __shared__ int order[kMaxSweepSites];
-    __shared__ double red[2][kSweep / kTile];
+    __shared__ unsigned char st[kMaxSweepSites], st_new[kMaxSweepSites], acc[kMaxSweepSites];
     const int b = blockIdx.x, t = threadIdx.x;
-    const int sa0 = sd.sys_sa_offset[b], nsa = sd.sys_sa_offset[b + 1] - sa0;
-    double* sx = s_sa;
-    double* sy = sx + nsa;
-    double* sz = sy + nsa;
-    double* sR = sz + nsa;
-    double* sA = sR + nsa;
-    double* sphi = sA + nsa;
-    for (int a = t; a < nsa; a += kSweep) {
-        const int g = sd.site_atoms[sa0 + a];
-        const double R = R64[g];
-        sx[a] = X[g]; sy[a] = Y[g]; sz[a] = Z[g];
-        sR[a] = R; sA[a] = A64[g];
-        sphi[a] = (double)(long long)phi_fx[sa0 + a] * (1.0 / kScaleP)
-                - gb_kd(R, kC, kT, kO, kap) * (double)Q[g] / R;
-    }
+    const int s0 = sd.sys_site_offset[b], S = sd.sys_site_offset[b + 1] - s0;
+    const double* C = couple + sd.sys_couple_offset[b];
     const double kTB = kKB * T_kelvin;
+    if (S <= kSweepCache)
+        for (int k = t; k < S * S; k += kSweep) sC[k] = C[k];
+    for (int i = t; i < S; i += kSweep) {
+        const int m = s0 + i, s = current_state[m], kind = sd.site_kind[m];
+        acc[i] = 0;
+        st[i] = st_new[i] = (unsigned char)s;
+        if (!(kinds & (1 << kind))) continue;
+        const int s_new = sweep_proposal(sd, m, s, u), g0 = sd.site_state_offset[m];
+        const double drive = kind == 0 ? kKB * T_kelvin * kLn10 * pH[b] : kFaraday * E_volt[b];
+        st_new[i] = (unsigned char)s_new;
+        su[i] = u[3 * (size_t)m + 2];
+        dg[i] = C[(size_t)i * S + i] + drive * (double)(sd.state_count[g0 + s_new] - sd.state_count[g0 + s])
+              - (sd.state_gref[g0 + s_new] - sd.state_gref[g0 + s]);
+    }
     for (int kind = 0; kind < 2; ++kind) {
         if (!(kinds & (1 << kind))) continue;
         const int o0 = kind == 0 ? sd.sys_prot_offset[b] : sd.sys_redox_offset[b];
@@ -2860,75 +2950,50 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
                 const double kj = order_key(mj);
                 rank += (kj < key) || (kj == key && mj < m);
             }
-            order[rank] = m;
+            order[rank] = m - s0;
         }
         __syncthreads();
-        const double drive = kind == 0 ? kKB * T_kelvin * kLn10 * pH[b] : kFaraday * E_volt[b];
         for (int v = 0; v < cnt; ++v) {
-            const int m = order[v];
-            const int a0 = sd.site_atom_offset[m] - sa0;
-            const int na = sd.site_atom_offset[m + 1] - sd.site_atom_offset[m];
-            const int g0 = sd.site_state_offset[m];
-            const int ns = sd.site_state_offset[m + 1] - g0;
-            const int s = current_state[m];
-            const int tp = pick_index(u[3 * (size_t)m + 1], ns - 1);
-            const int s_new = tp < s ? tp : tp + 1;
-            const double* qn = sd.state_charges + sd.state_charge_offset[g0 + s_new];
-            const double* qo = sd.state_charges + sd.state_charge_offset[g0 + s];
-            for (int a = t; a < na; a += kSweep) sdq[a] = qn[a] - qo[a];
-            __syncthreads();
-            double part[2] = {0.0, 0.0};
-            for (int a = t; a < na; a += kSweep) part[0] += sdq[a] * sphi[a0 + a];
-            const int n_tri = na * (na + 1) / 2;
-#pragma unroll 1
-            for (int p = t; p < n_tri; p += kSweep) {
-                int c = (int)((sqrt(8.0 * p + 1.0) - 1.0) * 0.5);
-                c += (c + 1) * (c + 2) / 2 <= p;
-                c -= c * (c + 1) / 2 > p;
-                const int a = p - c * (c + 1) / 2;
-                const int ia = a0 + a, ic = a0 + c;
-                const double K = (a == c) ? -gb_kd(sR[ia], kC, kT, kO, kap) / sR[ia]
-                                          : 2.0 * pairK(sx[ia] - sx[ic], sy[ia] - sy[ic], sz[ia] - sz[ic],
-                                                        sR[ia], sA[ia], sR[ic], sA[ic], kC, kT, kO, kap, cut2);
-                part[1] += sdq[a] * sdq[c] * K;
-            }
-            block_sum<2, kSweep / kTile>(red, part);
-            const double dE = part[0] + 0.5 * part[1];
-            const double dg = dE + drive * (double)(sd.state_count[g0 + s_new] - sd.state_count[g0 + s])
-                            - (sd.state_gref[g0 + s_new] - sd.state_gref[g0 + s]);
-            const bool acc = u[3 * (size_t)m + 2] < exp(-dg / kTB);
+            const int i = order[v];
+            const double d = dg[i];
+            const bool yes = su[i] < exp(-d / kTB);
             if (t == 0) {
-                if (accepted) accepted[m] = acc ? 1 : 0;
-                if (dG_out) dG_out[m] = dg;
-                if (counters) {
-                    counters[2 * (size_t)m] += 1;
-                    counters[2 * (size_t)m + 1] += acc ? 1 : 0;
-                }
-                if (acc) current_state[m] = s_new;
+                dg_at[i] = d;
+                acc[i] = yes;
             }
-            if (acc) {
-                // every site atom's potential gains K dq of this site
-                for (int i = t; i < nsa; i += kSweep) {
-                    double d = 0.0;
-                    for (int c = 0; c < na; ++c) {
-                        const int ic = a0 + c;
-                        d += sdq[c] * (i == ic ? -gb_kd(sR[i], kC, kT, kO, kap) / sR[i]
-                                               : pairK(sx[i] - sx[ic], sy[i] - sy[ic], sz[i] - sz[ic],
-                                                       sR[i], sA[i], sR[ic], sA[ic], kC, kT, kO, kap, cut2));
-                    }
-                    sphi[i] += d;
-                }
-                for (int a = t; a < na; a += kSweep) Qout[sd.site_atoms[sa0 + a0 + a]] = (T)qn[a];
-            }
+            if (!yes) continue;                         // the same for every thread
+            // the other sites' Delta G at the charges this visit leaves
+            const double* row = (S <= kSweepCache ? sC : C) + (size_t)i * S;
+            __syncthreads();
+            for (int k = t; k < S; k += kSweep)
+                if (k != i && (kinds & (1 << sd.site_kind[s0 + k]))) dg[k] += row[k];
             __syncthreads();
         }
+    }
+    __syncthreads();
+    for (int i = t; i < S; i += kSweep) {
+        const int m = s0 + i;
+        if (!(kinds & (1 << sd.site_kind[m]))) continue;
+        if (accepted) accepted[m] = acc[i];
+        if (dG_out) dG_out[m] = dg_at[i];
+        if (counters) {
+            counters[2 * (size_t)m] += 1;
+            counters[2 * (size_t)m + 1] += acc[i];
+        }
+        if (acc[i]) current_state[m] = st_new[i];
+    }
+    for (int i = 0; i < S; ++i) {
+        if (!acc[i]) continue;
+        const int m = s0 + i, a0 = sd.site_atom_offset[m], na = sd.site_atom_offset[m + 1] - a0;
+        const double* qn = sd.state_charges + sd.state_charge_offset[sd.site_state_offset[m] + st_new[i]];
+        for (int a = t; a < na; a += kSweep) Qout[sd.site_atoms[a0 + a]] = (T)qn[a];
     }
     if (t == 0 && n_electrons) {
         const int r0 = sd.sys_redox_offset[b], nr = sd.sys_redox_offset[b + 1] - r0;
         int ne = 0;
         for (int k = 0; k < nr; ++k) {
-            const int m = sd.sys_redox_sites[r0 + k];
-            ne += sd.state_count[sd.site_state_offset[m] + current_state[m]];
+            const int m = sd.sys_redox_sites[r0 + k], i = m - s0;
+            ne += sd.state_count[sd.site_state_offset[m] + (acc[i] ? st_new[i] : st[i])];
         }
         n_electrons[b] = ne;
     }
@@ -3269,12 +3334,12 @@ hipError_t launch_mc_step(const SiteDev& sd, int n_sys, const T* x, const T* y, 
 }
 
 template <typename T>
-hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int n_sa_max, const T* x, const T* y,
+hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, const T* x, const T* y,
                            const T* z, const T* q, T* q_out, const GBConst& c, const Work<T>& w,
-                           unsigned long long* phi_fx, int32_t* current_state, const double* pH,
-                           const double* E_volt, double T_kelvin, int kinds, const double* u,
-                           int32_t* n_electrons, int64_t* counters, int32_t* accepted, double* dG,
-                           hipStream_t s)
+                           unsigned long long* phi_fx, double* couple, int32_t* current_state,
+                           const double* pH, const double* E_volt, double T_kelvin, int kinds,
+                           const double* u, int32_t* n_electrons, int64_t* counters,
+                           int32_t* accepted, double* dG, hipStream_t s)
 {
     if (n_sys == 0) return hipSuccess;
     if (sd.n_rowitems > 0) {
@@ -3283,10 +3348,14 @@ hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int n_sa_max, const T* 
         hipLaunchKernelGGL(k_site_phi_rows<T>, dim3(sd.n_rowitems), dim3(kTile), 0, s, sd.rowitems,
                            sd.site_atoms, w.rows, q, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, w.ovf);
     }
-    const size_t lds = (size_t)6 * sizeof(double) * (size_t)(n_sa_max > 0 ? n_sa_max : 1);
-    hipLaunchKernelGGL(k_mc_sweep<T>, dim3(n_sys), dim3(kSweep), lds, s, sd, x, y, z, q, q_out, w.R64,
-                       w.A64, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state, pH, E_volt, T_kelvin, kinds, u,
-                       n_electrons, counters, accepted, dG);
+    if (sd.n_couples > 0)
+        hipLaunchKernelGGL(k_site_couple<T>, dim3(sd.n_couples), dim3(kCouple), 0, s, sd, x, y, z, q,
+                           w.R64, w.A64, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state,
+                           kinds, u, couple);
+    const size_t cached = (size_t)std::min(max_sites, kSweepCache);
+    hipLaunchKernelGGL(k_mc_sweep<T>, dim3(n_sys), dim3(kSweep), sizeof(double) * cached * cached, s, sd,
+                       q_out, couple, current_state, pH, E_volt, T_kelvin, kinds, u, n_electrons,
+                       counters, accepted, dG);
     return hipGetLastError();
 }
 
@@ -3328,7 +3397,7 @@ hipError_t launch_remd_exchange(int M, const double* E_rung, const int32_t* Ne, 
                                           int32_t*, hipStream_t, hipEvent_t*);                   \
     template hipError_t launch_mc_sweep<T>(const SiteDev&, int, int, const T*, const T*,          \
                                            const T*, const T*, T*, const GBConst&,               \
-                                           const Work<T>&, unsigned long long*, int32_t*,        \
+                                           const Work<T>&, unsigned long long*, double*, int32_t*, \
                                            const double*, const double*, double, int,            \
                                            const double*, int32_t*, int64_t*, int32_t*, double*, \
                                            hipStream_t);
