@@ -36,6 +36,7 @@
 namespace gbmc {
 
 #include "hct_poly.inc"
+#include "hct_vfar.inc"
 #include "hct_cut.inc"
 #include "exp2_poly.inc"
 
@@ -316,10 +317,25 @@ __device__ __forceinline__ void radii_pair(float xi, float yi, float zi, float x
     }
 }
 
+// Tiers of a tile, from the gap between its blocks (tile_tier): 0 some pair may
+// overlap; 1 all pairs take the polynomial form with y <= YFAR; 2 with y <= YVFAR.
+// Each tier takes the shortest fits that are as accurate as those of the tier
+// below.  (The FP32 descreening pass takes those of tier 1 in tier 2 as well.)
+template <int TIER>
+__device__ __forceinline__ float tier_p(float y)
+{
+    return TIER == 0 ? hct_poly_d(y) : TIER == 1 ? hct_poly_far(y) : hct_poly_vfar(y);
+}
+template <int TIER>
+__device__ __forceinline__ double tier_p(double y)
+{
+    return TIER == 0 ? hct_poly64(y) : TIER == 1 ? hct_poly64_far(y) : hct_poly64_vfar(y);
+}
+
 // The polynomial form alone, for walks that defer the pairs it does not cover
 // (as chain_pair_fast): a pair that needs the closed form in either direction
 // gets zero terms and, if act, its bit in mask.
-template <bool TEST = true>
+template <int TIER>
 __device__ __forceinline__ void radii_pair_fast(float xi, float yi, float zi, float xj, float yj,
                                                 float zj, float rti, float Si, float rtj, float Sj,
                                                 bool act, unsigned long long bit, float& hij,
@@ -333,6 +349,7 @@ __device__ __forceinline__ void radii_pair_fast(float xi, float yi, float zi, fl
     float xji = Si * invr, yji = xji * xji;
     // a separated tile (!TEST): every pair is non-overlapping with y <= YFAR,
     // where the short fit is as accurate as the wide one
+    constexpr bool TEST = TIER == 0;
     hij = xij * yij * invr * (TEST ? hct_poly(yij) : hct_poly_far(yij));
     hji = xji * yji * invr * (TEST ? hct_poly(yji) : hct_poly_far(yji));
     if constexpr (!TEST) return;
@@ -414,14 +431,17 @@ __device__ __forceinline__ void chain_pair(float r, float r2, float invr, float 
 // A pair that needs the closed form in either direction (act only) gets zero
 // terms and its bit in mask (one wave-uniform branch, taken only in the steps
 // that meet such a pair); the caller evaluates those pairs after the walk.
-// On separated tiles (TEST false, y <= YFAR) the factor (1 - y)^-2 comes from
-// its degree-5 fit, without a reciprocal.
-template <bool TEST = true>
+// On separated tiles the factor (1 - y)^-2 comes from its fit (degree 5 on tier
+// 1, 3 on tier 2), without a reciprocal.  Tier 2 holds 62 % of the tiles of a
+// 10,000-atom globule and 78 % of a 19,000-atom one, and saves six operations of
+// 57 on them.
+template <int TIER>
 __device__ __forceinline__ void chain_pair_fast(float r, float invr, float rti, float Si, float rtj,
                                                 float Sj, float bi, float bj, bool act,
                                                 unsigned long long bit, float& dEdr, float& gij2,
                                                 float& gji2, unsigned long long& mask)
 {
+    constexpr bool TEST = TIER == 0;
     const float u = invr * invr;
     const float xij = Sj * invr, yij = xij * xij;
     const float xji = Si * invr, yji = xji * xji;
@@ -431,12 +451,12 @@ __device__ __forceinline__ void chain_pair_fast(float r, float invr, float rti, 
         wij *= wij;
         wji *= wji;
     } else {
-        wij = hct_w_far(yij);
-        wji = hct_w_far(yji);
+        wij = TIER == 1 ? hct_w_far(yij) : hct_w_vfar(yij);
+        wji = TIER == 1 ? hct_w_far(yji) : hct_w_vfar(yji);
     }
     const float tij = yij * wij, tji = yji * wji;
-    float aij = xij * fmaf(yij, TEST ? hct_poly_d(yij) : hct_poly_far(yij), tij);
-    float aji = xji * fmaf(yji, TEST ? hct_poly_d(yji) : hct_poly_far(yji), tji);
+    float aij = xij * fmaf(yij, tier_p<TIER>(yij), tij);
+    float aji = xji * fmaf(yji, tier_p<TIER>(yji), tji);
     gij2 = tij * u;
     gji2 = tji * u;
     const bool fast = !TEST || ((r - Sj >= rti) & (yij <= GBMC_HCT_YMAX) & (r - Si >= rtj) &
@@ -493,7 +513,7 @@ __device__ __forceinline__ void chain_pair(double r, double r2, double invr, dou
 
 // FP64 forms of the two deferring pair functions (polynomial of degree 14 on
 // y <= 0.25; the pairs outside it are marked, as in FP32).
-template <bool TEST = true>
+template <int TIER>
 __device__ __forceinline__ void radii_pair_fast(double xi, double yi, double zi, double xj,
                                                 double yj, double zj, double rti, double Si,
                                                 double rtj, double Sj, bool act,
@@ -504,8 +524,9 @@ __device__ __forceinline__ void radii_pair_fast(double xi, double yi, double zi,
     dist64(xi, yi, zi, xj, yj, zj, r, invr);
     const double xij = Sj * invr, yij = xij * xij;
     const double xji = Si * invr, yji = xji * xji;
-    hij = xij * yij * invr * (TEST ? hct_poly64(yij) : hct_poly64_far(yij));
-    hji = xji * yji * invr * (TEST ? hct_poly64(yji) : hct_poly64_far(yji));
+    constexpr bool TEST = TIER == 0;
+    hij = xij * yij * invr * tier_p<TIER>(yij);
+    hji = xji * yji * invr * tier_p<TIER>(yji);
     if constexpr (!TEST) return;
     const bool fast = (r - Sj >= rti) & (yij <= GBMC_HCT_YMAX64) & (r - Si >= rtj) &
                       (yji <= GBMC_HCT_YMAX64);
@@ -517,7 +538,7 @@ __device__ __forceinline__ void radii_pair_fast(double xi, double yi, double zi,
     }
 }
 
-template <bool TEST = true>
+template <int TIER>
 __device__ __forceinline__ void chain_pair_fast(double r, double invr, double rti, double Si,
                                                 double rtj, double Sj, double bi, double bj,
                                                 bool act, unsigned long long bit, double& dEdr,
@@ -531,8 +552,9 @@ __device__ __forceinline__ void chain_pair_fast(double r, double invr, double rt
     rcp_pair(1.0 - yij, 1.0 - yji, wij, wji);
     wij *= wij;
     wji *= wji;
-    double aij = xij * yij * ((TEST ? hct_poly64(yij) : hct_poly64_far(yij)) + wij);   // -r^2 dH/dr
-    double aji = xji * yji * ((TEST ? hct_poly64(yji) : hct_poly64_far(yji)) + wji);
+    constexpr bool TEST = TIER == 0;
+    double aij = xij * yij * (tier_p<TIER>(yij) + wij);   // -r^2 dH/dr
+    double aji = xji * yji * (tier_p<TIER>(yji) + wji);
     gij2 = yij * wij * u;
     gji2 = yji * wji * u;
     const bool fast = !TEST || ((r - Sj >= rti) & (yij <= GBMC_HCT_YMAX64) & (r - Si >= rtj) &
@@ -911,6 +933,21 @@ __device__ __forceinline__ bool blocks_separated(const Q4<float>* __restrict__ b
     return g2 >= need * need && sm * sm <= 0.999f * ymax * g2;
 }
 
+// The tier of the tile of block X (and X + 1 for two rows) against block Y.
+// Tier 2 saves 5 of 55 instructions per pair of the FP32 chain walk and 8 of
+// every FP64 pair's multiply-adds for one more test per tile: the FP32 chain
+// pass over 64 systems of 1,024-19,488 atoms (70 % of the tiles) 5,558 -> 5,241
+// us.  The FP32 descreening pass would save 1 of 27 and lost 1.4 % to the test
+// (2,875 -> 2,915 us), so it stops at tier 1.
+template <int R>
+__device__ __forceinline__ int tile_tier(const Q4<float>* __restrict__ box, int X, int Y)
+{
+    if (!blocks_separated(box, X, Y, GBMC_HCT_YFAR)) return 0;
+    if (R == 2 && !blocks_separated(box, X + 1, Y, GBMC_HCT_YFAR)) return 0;
+    if (!blocks_separated(box, X, Y, GBMC_HCT_YVFAR)) return 1;
+    return R == 2 && !blocks_separated(box, X + 1, Y, GBMC_HCT_YVFAR) ? 1 : 2;
+}
+
 // Cutoff work items carry a tile mask: bit k set if j block J0 + k may hold a
 // pair within the cutoff (J1 <= J0 + 64).  The first such block at or after
 // J, or J1 if none.
@@ -1238,13 +1275,11 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
                                            int* __restrict__ ovf, unsigned long long tmask, T cR,
                                            const Q4<float>* __restrict__ box)
 {
-    // DEFER (one row, all pairs): overlapping pairs are marked during
-    // the walk and evaluated afterwards in packed rounds, as in the chain pass;
-    // tiles of separated blocks (blocks_separated) skip the per-pair test and
-    // take the short fit of H for y <= YFAR
-    constexpr bool DEFER = R == 1 && !CUT;
+    // DEFER (all pairs): overlapping pairs are marked during the walk and
+    // evaluated afterwards in packed rounds, as in the chain pass; tiles of
+    // separated blocks (tile_tier) skip the per-pair test and take short fits of H
+    constexpr bool DEFER = !CUT;
     [[maybe_unused]] const T icR = CUT ? T(1) / cR : T(0);
-    constexpr float kYfar = GBMC_HCT_YFAR;    // separated tiles: every pair has y <= this
     T xi[R], yi[R], zi[R], rti[R], Si[R];
     bool vi[R];
 #pragma unroll
@@ -1313,56 +1348,40 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
         auto load = [&](int s) { return JD{sj[s], sS[s]}; };
         int kstep = J == w.I ? 1 : 0;           // DEFER: walk step of the next pair
         unsigned long long dmask = 0ull;
-        auto pair_any = [&](const JD& d, int r, bool act, T (&acc)[1], auto sep_tag) {
-            constexpr bool SEP = decltype(sep_tag)::value;
-            T hij, hji;
-            if constexpr (CUT) {
-                // MODE 0: any cutoff; 1: cut_small tiles; 2: those separated
-                constexpr int MODE = decltype(sep_tag)::value;
-                if constexpr (MODE == 0)
+        // KIND: the tier of the tile; with a cutoff 0 (any cutoff), 1 (cut_small
+        // tiles) and 2 (those separated)
+        auto pair = [&](auto kind) {
+            return [&](const JD& d, int r, bool act, T (&acc)[1], bool) {
+                constexpr int KIND = decltype(kind)::value;
+                T hij, hji;
+                if constexpr (CUT && KIND == 0) {
                     radii_pair_cut(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r], Si[r], d.p.w,
                                    d.S, cR, hij, hji);
-                else
-                    radii_pair_cutf<MODE == 2>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r],
+                } else if constexpr (CUT) {
+                    radii_pair_cutf<KIND == 2>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r],
                                                Si[r], d.p.w, d.S, cR, icR, hij, hji);
-            } else if constexpr (DEFER) {
-                radii_pair_fast<!SEP>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r], Si[r],
-                                      d.p.w, d.S, act && vi[r], 1ull << kstep, hij, hji, dmask);
-                ++kstep;
-            } else {
-                radii_pair(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r], Si[r], d.p.w, d.S, hij,
-                           hji);
-            }
-            ai[r] += act ? hij : T(0);
-            acc[0] += act ? hji : T(0);
-        };
-        auto pair = [&](const JD& d, int r, bool act, T (&acc)[1], bool) {
-            pair_any(d, r, act, acc, std::false_type{});
-        };
-        auto pair_sep = [&](const JD& d, int r, bool act, T (&acc)[1], bool) {
-            pair_any(d, r, act, acc, std::true_type{});
-        };
-        if constexpr (CUT) {
-            auto pm = [&](auto mode) {
-                return [&, mode](const JD& d, int r, bool act, T (&acc)[1], bool) {
-                    pair_any(d, r, act, acc, mode);
-                };
+                } else {
+                    radii_pair_fast<KIND>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r], Si[r],
+                                          d.p.w, d.S, act && vi[r], 1ull << kstep, hij, hji, dmask);
+                    ++kstep;
+                }
+                ai[r] += act ? hij : T(0);
+                acc[0] += act ? hji : T(0);
             };
-            const int X = w.blk0 + w.I, Y = w.blk0 + J;
-            if (!cut_small(box, X, Y, (float)cR))
-                walk_tile<T, 1>(lane, J == w.I, aj, load, pm(std::integral_constant<int, 0>{}));
-            else if (J != w.I && blocks_separated(box, X, Y, kYfar))
-                walk_tile<T, 1>(lane, false, aj, load, pm(std::integral_constant<int, 2>{}));
-            else
-                walk_tile<T, 1>(lane, J == w.I, aj, load, pm(std::integral_constant<int, 1>{}));
-        } else if constexpr (R == 1) {
-            // wave-uniform: the blocks of the tile come from the item
-            if (DEFER && J != w.I && blocks_separated(box, w.blk0 + w.I, w.blk0 + J, kYfar))
-                walk_tile<T, 1>(lane, false, aj, load, pair_sep);
-            else
-                walk_tile<T, 1>(lane, J == w.I, aj, load, pair);
+        };
+        const int X = w.blk0 + w.I, Y = w.blk0 + J;      // wave-uniform, from the item
+        if (CUT && !cut_small(box, X, Y, (float)cR)) {
+            walk_tile<T, 1>(lane, J == w.I, aj, load, pair(std::integral_constant<int, 0>{}));
         } else {
-            walk_tile_rows2<T, 1>(lane, aj, load, pair);
+            const int tier = J == w.I ? 0
+                             : CUT || sizeof(T) == 4 ? blocks_separated(box, X, Y, GBMC_HCT_YFAR)
+                                                     : tile_tier<1>(box, X, Y);
+            if (tier == 0)
+                walk_tile<T, 1>(lane, J == w.I, aj, load, pair(std::integral_constant<int, CUT ? 1 : 0>{}));
+            else if (tier == 1)
+                walk_tile<T, 1>(lane, false, aj, load, pair(std::integral_constant<int, CUT ? 2 : 1>{}));
+            else if constexpr (!CUT && sizeof(T) == 8)
+                walk_tile<T, 1>(lane, false, aj, load, pair(std::integral_constant<int, 2>{}));
         }
         // DEFER: packed rounds of the marked pairs (see chain_item): j-side
         // terms through LDS integer atomics, i-side terms back to the i lane
@@ -1957,7 +1976,6 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
     // does not depend on the order of the rounds).
     constexpr bool DEFER = !CUT;
     [[maybe_unused]] const T icR = CUT ? T(1) / cR : T(0);
-    constexpr float kYfar = GBMC_HCT_YFAR;    // separated tiles: every pair has y <= this
     T xi[R], yi[R], zi[R], rti[R], Si[R], Bi[R], si[R];
     bool vi[R];
 #pragma unroll
@@ -2041,78 +2059,57 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
         unsigned long long dmask[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) dmask[r] = 0ull;
-        auto pair_any = [&](const JD& d, int r, bool act, T (&acc)[4], auto sep_tag) {
-            constexpr bool SEP = decltype(sep_tag)::value;
-            const Q4<T>& p = d.p;
-            const Q4<T>& b = d.b;
-            T dx = xi[r] - p.x, dy = yi[r] - p.y, dz = zi[r] - p.z;
-            T r2 = dist2(dx, dy, dz);
-            T invr = rsq(r2);
-            T rr = r2 * invr;
-            const T bj_ = act ? b.y : T(0);
-            const T bi_ = act ? Bi[r] : T(0);
-            T dEdr, gij2, gji2;
-            if constexpr (CUT) {
-                // the modes of the descreening pass
-                constexpr int MODE = decltype(sep_tag)::value;
-                if constexpr (MODE == 0)
+        // KIND as in the descreening pass
+        auto pair = [&](auto kind) {
+            return [&](const JD& d, int r, bool act, T (&acc)[4], bool) {
+                constexpr int KIND = decltype(kind)::value;
+                const Q4<T>& p = d.p;
+                const Q4<T>& b = d.b;
+                T dx = xi[r] - p.x, dy = yi[r] - p.y, dz = zi[r] - p.z;
+                T r2 = dist2(dx, dy, dz);
+                T invr = rsq(r2);
+                T rr = r2 * invr;
+                const T bj_ = act ? b.y : T(0);
+                const T bi_ = act ? Bi[r] : T(0);
+                T dEdr, gij2, gji2;
+                if constexpr (CUT && KIND == 0) {
                     chain_pair_cut(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, cR, dEdr, gij2,
                                    gji2, dri[r], acc[3]);
-                else
-                    chain_pair_cutf<MODE == 2>(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, cR,
+                } else if constexpr (CUT) {
+                    chain_pair_cutf<KIND == 2>(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, cR,
                                                icR, dEdr, gij2, gji2, dri[r], acc[3]);
-            } else if constexpr (DEFER) {
-                // only pairs of a real i atom are marked (padding lanes sit far
-                // apart, so none of theirs needs the closed form anyway)
-                chain_pair_fast<!SEP>(rr, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, act && vi[r],
-                                      1ull << kstep, dEdr, gij2, gji2, dmask[r]);
-                if (r == R - 1) ++kstep;            // a step serves every row of the item
-            } else {
-                chain_pair(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, dEdr, gij2, gji2,
-                           dri[r], acc[3]);
-            }
-            const T fr = dEdr * invr;
-            fxi[r] = fma(-fr, dx, fxi[r]);
-            fyi[r] = fma(-fr, dy, fyi[r]);
-            fzi[r] = fma(-fr, dz, fzi[r]);
-            dri[r] = fma(si[r] * bj_, gji2, dri[r]);
-            acc[0] = fma(fr, dx, acc[0]);
-            acc[1] = fma(fr, dy, acc[1]);
-            acc[2] = fma(fr, dz, acc[2]);
-            acc[3] = fma(b.z * bi_, gij2, acc[3]);
-        };
-        auto pair = [&](const JD& d, int r, bool act, T (&acc)[4], bool) {
-            pair_any(d, r, act, acc, std::false_type{});
-        };
-        auto pair_sep = [&](const JD& d, int r, bool act, T (&acc)[4], bool) {
-            pair_any(d, r, act, acc, std::true_type{});
-        };
-        if constexpr (CUT) {
-            auto pm = [&](auto mode) {
-                return [&, mode](const JD& d, int r, bool act, T (&acc)[4], bool) {
-                    pair_any(d, r, act, acc, mode);
-                };
+                } else {
+                    // only pairs of a real i atom are marked (padding lanes sit far
+                    // apart, so none of theirs needs the closed form anyway)
+                    chain_pair_fast<KIND>(rr, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, act && vi[r],
+                                          1ull << kstep, dEdr, gij2, gji2, dmask[r]);
+                    if (r == R - 1) ++kstep;        // a step serves every row of the item
+                }
+                const T fr = dEdr * invr;
+                fxi[r] = fma(-fr, dx, fxi[r]);
+                fyi[r] = fma(-fr, dy, fyi[r]);
+                fzi[r] = fma(-fr, dz, fzi[r]);
+                dri[r] = fma(si[r] * bj_, gji2, dri[r]);
+                acc[0] = fma(fr, dx, acc[0]);
+                acc[1] = fma(fr, dy, acc[1]);
+                acc[2] = fma(fr, dz, acc[2]);
+                acc[3] = fma(b.z * bi_, gij2, acc[3]);
             };
-            const int X = w.blk0 + w.I, Y = w.blk0 + J;
-            if (!cut_small(wk.box, X, Y, (float)cR))
-                walk_tile<T, 4>(lane, J == w.I, aj, load, pm(std::integral_constant<int, 0>{}));
-            else if (J != w.I && blocks_separated(wk.box, X, Y, kYfar))
-                walk_tile<T, 4>(lane, false, aj, load, pm(std::integral_constant<int, 2>{}));
-            else
-                walk_tile<T, 4>(lane, J == w.I, aj, load, pm(std::integral_constant<int, 1>{}));
-        } else if constexpr (R == 1) {
-            // separated blocks (wave-uniform): no pair needs the closed form
-            if (DEFER && J != w.I && blocks_separated(wk.box, w.blk0 + w.I, w.blk0 + J, kYfar))
-                walk_tile<T, 4>(lane, false, aj, load, pair_sep);
-            else
-                walk_tile<T, 4>(lane, J == w.I, aj, load, pair);
+        };
+        // two-row items hold no diagonal tile
+        const bool diagonal = R == 1 && J == w.I;
+        auto walk = [&](auto kind, bool diag) {
+            if constexpr (R == 1) walk_tile<T, 4>(lane, diag, aj, load, pair(kind));
+            else walk_tile_rows2<T, 4>(lane, aj, load, pair(kind));
+        };
+        const int X = w.blk0 + w.I, Y = w.blk0 + J;      // wave-uniform, from the item
+        if (CUT && !cut_small(wk.box, X, Y, (float)cR)) {
+            walk(std::integral_constant<int, 0>{}, diagonal);
         } else {
-            // two rows (never a diagonal tile): separated if both rows' tiles are
-            if (DEFER && blocks_separated(wk.box, w.blk0 + w.I, w.blk0 + J, kYfar) &&
-                blocks_separated(wk.box, w.blk0 + w.I + 1, w.blk0 + J, kYfar))
-                walk_tile_rows2<T, 4>(lane, aj, load, pair_sep);
-            else
-                walk_tile_rows2<T, 4>(lane, aj, load, pair);
+            const int tier = diagonal ? 0 : tile_tier<R>(wk.box, X, Y);
+            if (tier == 0) walk(std::integral_constant<int, CUT ? 1 : 0>{}, diagonal);
+            else if (CUT || tier == 1) walk(std::integral_constant<int, CUT ? 2 : 1>{}, false);
+            else if constexpr (!CUT) walk(std::integral_constant<int, 2>{}, false);
         }
         // DEFER: the marked pairs, packed into rounds of up to 64 (the marks of
         // all lanes listed in lane order, lane t of a round taking list entry
@@ -2246,8 +2243,10 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
     }
 }
 
+// (All-pairs FP32: the waves per SIMD that the walk needs, 5 for single-tile and 4
+// for long items; left alone the compiler takes a few registers too many.)
 template <typename T, int W, bool CUT, bool ONE>
-__global__ __launch_bounds__(kTile * W) void k_chain_pairs(
+__global__ __launch_bounds__(kTile * W, sizeof(T) == 4 && !CUT ? (ONE ? 5 : 4) : 1) void k_chain_pairs(
     const WorkItem* __restrict__ items, int n_items, const Q4<T>* __restrict__ P,
     const Q4<T>* __restrict__ Gx, Work<T> wk, T cR)
 {

@@ -117,10 +117,12 @@ __device__ __forceinline__ void radii_atom(const WorkItem& w, int a, const Q4<T>
     }
 }
 
-template <typename T, bool SEP>
+template <typename T, int TIER>
 __device__ __forceinline__ void radii_wide_walk(RadiiWide<T>& L, int wave, int lane, bool diagonal,
                                                 bool vi, T& sum)
 {
+    constexpr bool SEP = TIER != 0;
+    constexpr int FIT = sizeof(T) == 4 && SEP ? 1 : TIER;
     T me[5];
 #pragma unroll
     for (int a = 0; a < 5; ++a) me[a] = L.i[a][lane];
@@ -142,12 +144,12 @@ __device__ __forceinline__ void radii_wide_walk(RadiiWide<T>& L, int wave, int l
             const T xij = S * invr, yij = xij * xij;
             const T xji = me[4] * invr, yji = xji * xji;
             L.term[0][s][lane] = xij * yij * invr;
-            L.term[1][s][lane] = hct_p<true>(yij);
+            L.term[1][s][lane] = tier_p<FIT>(yij);
             L.term[2][s][lane] = xji * yji * invr;
-            L.term[3][s][lane] = hct_p<true>(yji);
+            L.term[3][s][lane] = tier_p<FIT>(yji);
         } else {
             T hij, hji;
-            radii_pair_fast<true>(me[0], me[1], me[2], x, y, z, me[3], me[4], rt, S, act && vi,
+            radii_pair_fast<0>(me[0], me[1], me[2], x, y, z, me[3], me[4], rt, S, act && vi,
                                   1ull << k, hij, hji, marks);
             L.term[0][s][lane] = act ? hij : T(0);
             L.term[2][s][lane] = act ? hji : T(0);
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(kWide * kTile) void k_radii_wide(
     const WorkItem w = items[blockIdx.x];
     const int J = w.J0, i = w.I * kTile + lane, j = J * kTile + lane;
     const bool diagonal = J == w.I;
-    const bool sep = !diagonal && blocks_separated(box, w.blk0 + w.I, w.blk0 + J, GBMC_HCT_YFAR);
+    const int tier = diagonal ? 0 : tile_tier<1>(box, w.blk0 + w.I, w.blk0 + J);
     if (wave < 2) {
         T v[5];
         radii_atom<T>(w, wave == 0 ? j : i, P, Gx, v);
@@ -199,10 +201,12 @@ __global__ __launch_bounds__(kWide * kTile) void k_radii_wide(
     __syncthreads();
     T sum = T(0);
     bool bad = false, deferred = false;
-    if (sep) {
-        radii_wide_walk<T, true>(L, wave, lane, false, true, sum);
+    if (tier == 2) {
+        radii_wide_walk<T, 2>(L, wave, lane, false, true, sum);
+    } else if (tier == 1) {
+        radii_wide_walk<T, 1>(L, wave, lane, false, true, sum);
     } else {
-        radii_wide_walk<T, false>(L, wave, lane, diagonal, i < w.n, sum);
+        radii_wide_walk<T, 0>(L, wave, lane, diagonal, i < w.n, sum);
         __syncthreads();
         T* siv = &L.term[0][0][0];
         deferred = wide_deferred<1>(
@@ -436,7 +440,7 @@ struct ChainWide {
 template <int R>
 constexpr int chain_tasks_per = (4 * R + 4 + kWide - 1) / kWide;
 
-template <typename T, int R, bool SEP>
+template <typename T, int R, int TIER>
 __device__ __forceinline__ void chain_wide_walk(ChainWide<T>& L, int wave, int lane, bool diagonal,
                                                 const bool (&vi)[R],
                                                 T (&sum)[chain_tasks_per<R>])
@@ -457,7 +461,7 @@ __device__ __forceinline__ void chain_wide_walk(ChainWide<T>& L, int wave, int l
         const T invr = rsq(r2);
         const T rr = r2 * invr;
         T dEdr, gij, gji;
-        chain_pair_fast<!SEP>(rr, invr, me[r][3], me[r][4], L.j[3][l], L.j[4][l], me[r][5], L.j[5][l],
+        chain_pair_fast<TIER>(rr, invr, me[r][3], me[r][4], L.j[3][l], L.j[4][l], me[r][5], L.j[5][l],
                               act && vi[r], 1ull << k, dEdr, gij, gji, marks[r]);
         L.term[0][q][lane] = act ? T(dEdr * invr) : T(0);
         L.term[1][q][lane] = act ? gij : T(0);
@@ -503,7 +507,7 @@ __device__ __forceinline__ void chain_wide_walk(ChainWide<T>& L, int wave, int l
         for (int u = 0; u < chain_tasks_per<R>; ++u)
             if (wave + u * kWide < 4 * R + 4) run_task(wave + u * kWide, sum[u], k0);
     });
-    if constexpr (!SEP)
+    if constexpr (TIER == 0)
 #pragma unroll
         for (int r = 0; r < R; ++r)
             if (marks[r] != 0ull) atomicOr(&L.mask[r * kTile + lane], marks[r]);
@@ -516,9 +520,7 @@ __device__ __forceinline__ void chain_wide(ChainWide<T>& L, const WorkItem& w, i
 {
     const int J = w.J0, j = J * kTile + lane;
     const bool diagonal = R == 1 && J == w.I;
-    const int X = w.blk0 + w.I, Y = w.blk0 + J;
-    const bool sep = !diagonal && blocks_separated(wk.box, X, Y, GBMC_HCT_YFAR) &&
-                     (R == 1 || blocks_separated(wk.box, X + 1, Y, GBMC_HCT_YFAR));
+    const int tier = diagonal ? 0 : tile_tier<R>(wk.box, w.blk0 + w.I, w.blk0 + J);
     if (wave <= R) {
         const int a = wave == 0 ? j : (w.I + wave - 1) * kTile + lane;
         T v[7];
@@ -551,10 +553,12 @@ __device__ __forceinline__ void chain_wide(ChainWide<T>& L, const WorkItem& w, i
 #pragma unroll
     for (int r = 0; r < R; ++r) vi[r] = (w.I + r) * kTile + lane < w.n;
     bool bad = false, deferred = false;
-    if (sep) {
-        chain_wide_walk<T, R, true>(L, wave, lane, false, vi, sum);
+    if (tier == 2) {
+        chain_wide_walk<T, R, 2>(L, wave, lane, false, vi, sum);
+    } else if (tier == 1) {
+        chain_wide_walk<T, R, 1>(L, wave, lane, false, vi, sum);
     } else {
-        chain_wide_walk<T, R, false>(L, wave, lane, diagonal, vi, sum);
+        chain_wide_walk<T, R, 0>(L, wave, lane, diagonal, vi, sum);
         __syncthreads();
         T* siv = &L.term[0][0][0];              // [4][kWindow]
         static_assert(sizeof(L.term) >= 4 * kWindow * sizeof(T), "room for a round's terms");
