@@ -812,7 +812,8 @@ static bool uses_cutoffs(const GBConst& c) { return c.rgbmax > 0.0 || c.cutoff >
 static PassShape pass_shape(const gbmc_plan* p, int k)
 {
     return PassShape{p->d_items[k], p->n_items[k], p->tuning.waves_per_group[k],
-                     p->tuning.j_blocks_per_item[k] == 1, p->wide[k]};
+                     p->tuning.j_blocks_per_item[k] == 1, p->wide[k],
+                     p->d_total + (size_t)k * p->n_blocks};
 }
 
 static QueueShape queue_shape(const gbmc_plan* p)
@@ -856,7 +857,7 @@ extern "C" {
 // staging also packs the charges and clears the energy and chain passes'
 // accumulators, so that the energy call that follows stages nothing.
 static hipError_t radii_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst& c, void* ws,
-                               void* born_R, hipStream_t s, bool with_q)
+                               void* born_R, hipStream_t s, bool with_q, bool finalize)
 {
     hipEvent_t* ev = p->n_items[GBMC_PASS_RADII] > 0 ? events(p, {kKRadii}) : nullptr;
     if (p->prec == GBMC_FP32_FIXED)
@@ -865,19 +866,21 @@ static hipError_t radii_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst&
                                    (const float*)a->z, (const float*)a->rho,
                                    (const float*)a->screen, c, carve<float>(p, ws),
                                    (float*)born_R, s, ev,
-                                   with_q ? (const float*)a->q : nullptr);
+                                   with_q ? (const float*)a->q : nullptr, finalize);
     return launch_radii<double>(pass_shape(p, GBMC_PASS_RADII), p->n_atoms, cut_plan(p),
                                 (const double*)a->x, (const double*)a->y,
                                 (const double*)a->z, (const double*)a->rho,
                                 (const double*)a->screen, c, carve<double>(p, ws),
-                                (double*)born_R, s, ev, with_q ? (const double*)a->q : nullptr);
+                                (double*)born_R, s, ev, with_q ? (const double*)a->q : nullptr,
+                                finalize);
 }
 
 // The energy pass (and the chain pass when force or dEdrho is requested);
 // staged: the preceding radii launch of the same call staged the charges.
 static hipError_t energy_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst& c, void* ws,
                                 double* e_coul, double* e_gb, void* force, void* dEdq,
-                                void* dEdrho, hipStream_t s, bool staged)
+                                void* dEdrho, hipStream_t s, bool staged, bool finalize,
+                                void* born_R)
 {
     const bool chain = force || dEdrho;
     hipEvent_t* ev = nullptr;
@@ -890,13 +893,15 @@ static hipError_t energy_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst
                                            (const float*)a->z, (const float*)a->q,
                                            (const float*)a->rho, (const float*)a->screen, c,
                                            carve<float>(p, ws), e_coul, e_gb, (float*)force,
-                                           (float*)dEdq, (float*)dEdrho, s, ev, staged);
+                                           (float*)dEdq, (float*)dEdrho, s, ev, staged, finalize,
+                                           (float*)born_R);
     return launch_energy_forces<double>(pe, pc, p->n_atoms, p->d_sums, p->n_sums, cut_plan(p),
                                         (const double*)a->x, (const double*)a->y,
                                         (const double*)a->z, (const double*)a->q,
                                         (const double*)a->rho, (const double*)a->screen, c,
                                         carve<double>(p, ws), e_coul, e_gb, (double*)force,
-                                        (double*)dEdq, (double*)dEdrho, s, ev, staged);
+                                        (double*)dEdq, (double*)dEdrho, s, ev, staged, finalize,
+                                        (double*)born_R);
 }
 
 gbmc_status gb_radii(gbmc_plan* p, const gbmc_atoms* a, const gbmc_gb_params* gp, void* ws,
@@ -904,7 +909,7 @@ gbmc_status gb_radii(gbmc_plan* p, const gbmc_atoms* a, const gbmc_gb_params* gp
 {
     gbmc_status st = check_call(p, a, gp, ws, false);
     if (st != GBMC_OK || p->n_atoms == 0) return st;
-    hipError_t e = radii_launch(p, a, make_const(gp), ws, born_R, s, false);
+    hipError_t e = radii_launch(p, a, make_const(gp), ws, born_R, s, false, true);
     return e == hipSuccess ? GBMC_OK : hip_fail(e, "gb_radii launch");
 }
 
@@ -915,7 +920,7 @@ gbmc_status gb_energy_forces(gbmc_plan* p, const gbmc_atoms* a, const gbmc_gb_pa
     gbmc_status st = check_call(p, a, gp, ws, true);
     if (st != GBMC_OK) return st;
     hipError_t e = energy_launch(p, a, make_const(gp), ws, e_coul, e_gb, force, dEdq, dEdrho, s,
-                                 false);
+                                 false, false, nullptr);
     return e == hipSuccess ? GBMC_OK : hip_fail(e, "gb_energy_forces launch");
 }
 
@@ -950,11 +955,14 @@ static gbmc_status evaluate_impl(gbmc_plan* p, const gbmc_atoms* a, const gbmc_g
         if (e != hipSuccess) return hip_fail(e, "gb_evaluate launch");
         return mark();
     }
-    hipError_t e = radii_launch(p, a, c, ws, born_R, s, true);
+    // the wide energy pass can form the radii itself: one launch fewer
+    const bool late = p->wide[GBMC_PASS_ENERGY] && !uses_cutoffs(c) && !use_fork;
+    hipError_t e = radii_launch(p, a, c, ws, born_R, s, true, !late);
     if (e != hipSuccess) return hip_fail(e, "gb_evaluate launch");
     st = mark();
     if (st != GBMC_OK) return st;
-    e = energy_launch(p, a, c, ws, e_coul, e_gb, force, dEdq, dEdrho, s, true);
+    e = energy_launch(p, a, c, ws, e_coul, e_gb, force, dEdq, dEdrho, s, true, late,
+                      born_R);
     return e == hipSuccess ? GBMC_OK : hip_fail(e, "gb_evaluate launch");
 }
 

@@ -212,20 +212,22 @@ struct PassShape {
     int waves_per_group;
     bool one_tile;          // every item is a single tile (one j block per item)
     bool wide;              // one workgroup per item (gbmc_wide.h; single tiles, all pairs)
+    const int32_t* total;   // [n_blocks] items that touch each block
 };
 
 template <typename T>
 hipError_t launch_radii(const PassShape& radii, int n_atoms, const CutPlan& cp,
                         const T* x, const T* y, const T* z, const T* rho, const T* screen,
                         const GBConst& c, const Work<T>& w, T* born_R, hipStream_t s,
-                        hipEvent_t* ev, const T* q = nullptr);
+                        hipEvent_t* ev, const T* q = nullptr, bool finalize = true);
 template <typename T>
 hipError_t launch_energy_forces(const PassShape& energy, const PassShape& chain, int n_atoms,
                                 const SumSpan* sums, int n_sums, const CutPlan& cp,
                                 const T* x, const T* y, const T* z, const T* q, const T* rho,
                                 const T* screen, const GBConst& c, const Work<T>& w,
                                 double* e_coul, double* e_gb, T* force, T* dEdq, T* dEdrho,
-                                hipStream_t s, hipEvent_t* ev, bool staged = false);
+                                hipStream_t s, hipEvent_t* ev, bool staged = false,
+                                bool finalize = false, T* born_R = nullptr);
 // Ints of the workspace taken by the queued launch's ticket counter and error
 // word (on separate 128-byte lines).
 constexpr int kQueueWords = 64;

@@ -1059,7 +1059,7 @@ __device__ __forceinline__ void walk_tile_rows2(int lane, T (&acc_j)[NJ], Load&&
 // ============================================================ staging
 // Packs the caller's SoA inputs into the plan's processing order (a spatial
 // order keeps overlapping pairs inside few tiles): P = (x, y, z, q),
-// Gx = (rt, S, screen, 0) with rt = rho - offset and S = screen rt.  One wave
+// Gx = (rt, S, screen, rho) with rt = rho - offset and S = screen rt.  One wave
 // per 64-atom block: lane l stages atom l of the block, and the wave writes
 // the block's coordinate box with its largest S and rt (box[2b]: lowest x, y,
 // z and S; box[2b + 1]: highest x, y, z and rt), from which the pair passes
@@ -1090,10 +1090,10 @@ __global__ __launch_bounds__(256) void k_stage(const BlockSpan* __restrict__ blo
     p.x = X[c]; p.y = Y[c]; p.z = Z[c];
     p.w = Q ? Q[c] : T(0);
     Q4<T> g;
-    g.x = RHO[c] - offset;
+    g.w = RHO[c];
+    g.x = g.w - offset;
     g.z = SCR[c];
     g.y = g.z * g.x;
-    g.w = T(0);
     if (own) {
         // the call's fixed-point accumulators of atom k ([n_acc][N] each) start at zero
         for (int a = 0; a < z.n_acc0; ++a) z.acc0[(size_t)a * n_atoms + k] = 0ull;
@@ -1495,45 +1495,61 @@ __global__ __launch_bounds__(kTile * W) void k_radii_pairs(
 // Per atom: OBC radius from the descreening sum (FP64), and the per-atom state
 // of the later passes (FP64 state in caller order, pair-precision copies in
 // internal order).
-template <typename T>
-__device__ __forceinline__ void radii_final_atom(int k, const T* __restrict__ RHO, const GBConst& c,
-                                                 const Work<T>& w, T* __restrict__ born_R)
+struct RadiusState {
+    double I, t, R, dRdPsi;
+};
+
+// (Fused operations where a product meets a sum, so that every kernel that forms
+// a radius rounds alike.)
+__device__ __forceinline__ RadiusState radius_state(unsigned long long I_fx, double rho, const GBConst& c)
 {
-    const int g = w.perm[k];
-    double rho = (double)RHO[g];
-    double rt = rho - c.offset;
-    double I = (double)(long long)ld_dev(w.I_fx + k) * (1.0 / kScaleI);
-    double psi = rt * I;
-    double th = c.alpha * psi - c.beta * psi * psi + c.gamma * psi * psi * psi;
-    double t = tanh(th);
-    double R = 1.0 / (1.0 / rt - t / rho);
-    w.I64[g] = I;
-    w.R64[g] = R;
-    w.A64[g] = 0.5 / R;
-    w.T64[g] = t;
-    const double dRdPsi =
-        R * R * (1.0 - t * t) * (c.alpha - 2.0 * c.beta * psi + 3.0 * c.gamma * psi * psi) / rho;
-    st_dev(w.dRdPsi64 + g, dRdPsi);
-    st_dev(w.dRdPsi_p + k, dRdPsi);
-    st_dev(w.R_t + k, (T)R);
-    st_dev(w.a_t + k, (T)(kAScale / R));
+    RadiusState st;
+    const double rt = rho - c.offset;
+    st.I = (double)(long long)I_fx * (1.0 / kScaleI);
+    const double psi = rt * st.I;
+    st.t = tanh(psi * fma(psi, fma(psi, c.gamma, -c.beta), c.alpha));
+    st.R = 1.0 / (1.0 / rt - st.t / rho);
+    st.dRdPsi = st.R * st.R * fma(-st.t, st.t, 1.0) *
+                fma(psi, fma(psi, 3.0 * c.gamma, -2.0 * c.beta), c.alpha) / rho;
+    return st;
+}
+
+// Stores the state of atom k (processing order), which is atom g of the caller.
+template <typename T>
+__device__ __forceinline__ void radius_store(int k, int g, const RadiusState& st, const Q4<T>& p,
+                                             const Work<T>& w, T* __restrict__ born_R)
+{
+    w.I64[g] = st.I;
+    w.R64[g] = st.R;
+    w.A64[g] = 0.5 / st.R;
+    w.T64[g] = st.t;
+    st_dev(w.dRdPsi64 + g, st.dRdPsi);
+    st_dev(w.dRdPsi_p + k, st.dRdPsi);
+    st_dev(w.R_t + k, (T)st.R);
+    st_dev(w.a_t + k, (T)(kAScale / st.R));
     // FP64 record of the atom for the Monte Carlo kernels (caller order)
-    const Q4<T> p = w.P[k];
     Row64 row;
     row.x = (double)p.x; row.y = (double)p.y; row.z = (double)p.z;
-    row.R = R; row.A = 0.5 / R;
+    row.R = st.R; row.A = 0.5 / st.R;
     row.pad0 = row.pad1 = row.pad2 = 0.0;
     w.rows[g] = row;
-    if (born_R) born_R[g] = (T)R;
+    if (born_R) born_R[g] = (T)st.R;
 }
 
 template <typename T>
-__global__ void k_radii_finalize(int n_atoms, const T* __restrict__ RHO, GBConst c, Work<T> w,
-                                 T* __restrict__ born_R)
+__device__ __forceinline__ void radii_final_atom(int k, const GBConst& c, const Work<T>& w,
+                                                 T* __restrict__ born_R)
+{
+    const RadiusState st = radius_state(ld_dev(w.I_fx + k), (double)w.Gx[k].w, c);
+    radius_store<T>(k, w.perm[k], st, w.P[k], w, born_R);
+}
+
+template <typename T>
+__global__ void k_radii_finalize(int n_atoms, GBConst c, Work<T> w, T* __restrict__ born_R)
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_atoms) return;
-    radii_final_atom<T>(k, RHO, c, w, born_R);
+    radii_final_atom<T>(k, c, w, born_R);
 }
 
 // ================================================================ pass 2
@@ -2243,6 +2259,47 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
     }
 }
 
+// Outputs of an evaluation with the chain pass (any pointer may be NULL), and the
+// energy spans summed for it.
+template <typename T>
+struct PostOut {
+    const SumSpan* sums;
+    int n_sum;
+    double *e_coul, *e_gb;
+    T *dEdq, *force, *dEdrho;
+    double offset;
+};
+
+// One atom's dE/dq, force and dE/drho (caller order) from its final sums:
+//   dE/drho_k = G_k R_k^2 (1/rt_k^2 - T_k/rho_k^2) + B_k I_k + (pair part)
+// LATE: the chain pass's sums are those of the running launch, complete but
+// possibly not in this XCD's cache.
+template <typename T, bool LATE>
+__device__ __forceinline__ void post_atom(int k, const PostOut<T>& o, const Work<T>& w)
+{
+    auto sum = [&](const unsigned long long* p) {
+        return (double)(long long)(LATE ? ld_dev(p) : *p) * (1.0 / kScaleF);
+    };
+    const int g = w.perm[k];
+    if (o.dEdq) o.dEdq[g] = (T)((double)(long long)w.phi_fx[k] * (1.0 / kScaleF));
+    if (o.force) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            o.force[3 * (size_t)g + a] = (T)sum(w.F_fx + (size_t)a * w.n_atoms + k);
+    }
+    if (o.dEdrho) {
+        const double rho = (double)w.Gx[k].w;
+        const double rt = rho - o.offset;
+        const double R = w.R64[g];
+        // G = dE/dR from its fixed-point sum and the chain weight B = G dR/dPsi
+        const double G = (double)(long long)w.G_fx[k] * (1.0 / kScaleF);
+        const double B = G * w.dRdPsi64[g];
+        const double v = fma(G * R * R, 1.0 / (rt * rt) - w.T64[g] / (rho * rho), B * w.I64[g]) +
+                         sum(w.drho_fx + k);
+        o.dEdrho[g] = (T)v;
+    }
+}
+
 // (All-pairs FP32: the waves per SIMD that the walk needs, 5 for single-tile and 4
 // for long items; left alone the compiler takes a few registers too many.)
 template <typename T, int W, bool CUT, bool ONE>
@@ -2405,7 +2462,7 @@ struct PLds {
 
 template <typename T, int W, int P0, int P1, bool GRAD, bool SALT, bool ONE>
 __global__ __launch_bounds__(kTile * W) void k_pairs_queue(
-    PQueue q, const T* __restrict__ RHO, GBConst c, T kC, T kT, SaltK<T> sk, Work<T> wk,
+    PQueue q, GBConst c, T kC, T kT, SaltK<T> sk, Work<T> wk,
     T* __restrict__ born_R)
 {
     __shared__ __align__(16) unsigned char lds_w[W][PLds<T>::bytes];
@@ -2439,7 +2496,7 @@ __global__ __launch_bounds__(kTile * W) void k_pairs_queue(
                                 T(0), wk.box);
         pq_complete(q, 0, w, lane, [&](int L) {
             const int i = L * kTile + lane;
-            if (i < w.n) radii_final_atom<T>(w.base + i, RHO, c, wk, born_R);
+            if (i < w.n) radii_final_atom<T>(w.base + i, c, wk, born_R);
         });
     } else if (P0 <= 1 && P1 >= 1 && p == 1) {
         const CutK<T> ck{T(0), T(0)};
@@ -2469,41 +2526,17 @@ __global__ __launch_bounds__(kTile * W) void k_pairs_queue(
 
 // After the chain pass (three launches, or the queued launch): blocks
 // [0, n_sum) sum the energy shares (one span each); the following blocks write one atom's
-// outputs per thread: dE/dq, the forces and dE/drho (caller order).
-//   dE/drho_k = G_k R_k^2 (1/rt_k^2 - T_k/rho_k^2) + B_k I_k + (pair part)
+// outputs per thread.
 template <typename T>
-__global__ __launch_bounds__(256) void k_post(int n_atoms, const SumSpan* __restrict__ sums,
-                                              int n_sum, Work<T> w, double* __restrict__ e_coul,
-                                              double* __restrict__ e_gb, T* __restrict__ dEdq,
-                                              T* __restrict__ force, T* __restrict__ dEdrho,
-                                              const T* __restrict__ RHO, double offset)
+__global__ __launch_bounds__(256) void k_post(int n_atoms, PostOut<T> o, Work<T> w)
 {
     const int t = threadIdx.x;
-    if ((int)blockIdx.x < n_sum) {
-        sum_energies<T>(sums[blockIdx.x], w, e_coul, e_gb);
+    if ((int)blockIdx.x < o.n_sum) {
+        sum_energies<T>(o.sums[blockIdx.x], w, o.e_coul, o.e_gb);
         return;
     }
-    const int k = ((int)blockIdx.x - n_sum) * 256 + t;
-    if (k >= n_atoms) return;
-    const int g = w.perm[k];
-    if (dEdq) dEdq[g] = (T)((double)(long long)w.phi_fx[k] * (1.0 / kScaleF));
-    if (force) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            force[3 * (size_t)g + a] = (T)((double)(long long)w.F_fx[a * w.n_atoms + k] * (1.0 / kScaleF));
-    }
-    if (dEdrho) {
-        double rho = (double)RHO[g];
-        double rt = rho - offset;
-        double R = w.R64[g];
-        // G = dE/dR from its fixed-point sum and the chain weight B = G dR/dPsi
-        const double G = (double)(long long)w.G_fx[k] * (1.0 / kScaleF);
-        const double B = G * w.dRdPsi64[g];
-        double v = G * R * R * (1.0 / (rt * rt) - w.T64[g] / (rho * rho))
-                 + B * w.I64[g]
-                 + (double)(long long)w.drho_fx[k] * (1.0 / kScaleF);
-        dEdrho[g] = (T)v;
-    }
+    const int k = ((int)blockIdx.x - o.n_sum) * 256 + t;
+    if (k < n_atoms) post_atom<T, false>(k, o, w);
 }
 
 // ============================================================ Monte Carlo
@@ -3116,7 +3149,7 @@ template <typename T>
 hipError_t launch_radii(const PassShape& pr, int n_atoms, const CutPlan& cp,
                         const T* x, const T* y, const T* z, const T* rho, const T* screen,
                         const GBConst& c, const Work<T>& w, T* born_R, hipStream_t s,
-                        hipEvent_t* ev, const T* q)
+                        hipEvent_t* ev, const T* q, bool finalize)
 {
     if (n_atoms == 0) return hipSuccess;
     // staging also clears I_fx and the overflow flags: every evaluation starts
@@ -3148,8 +3181,9 @@ hipError_t launch_radii(const PassShape& pr, int n_atoms, const CutPlan& cp,
                                               pr.items, pr.n_items, w.citems[0], w.ccount, w.P, w.Gx,
                                               w.I_fx, w.ovf, (T)0, w.box))
     }
-    hipLaunchKernelGGL(k_radii_finalize<T>, dim3(blocks_for(n_atoms, 256)), dim3(256), 0, s, n_atoms,
-                       rho, c, w, born_R);
+    if (finalize)
+        hipLaunchKernelGGL(k_radii_finalize<T>, dim3(blocks_for(n_atoms, 256)), dim3(256), 0, s, n_atoms,
+                           c, w, born_R);
     return hipGetLastError();
 }
 
@@ -3159,7 +3193,7 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
                                 const T* x, const T* y, const T* z, const T* q, const T* rho,
                                 const T* screen, const GBConst& c, const Work<T>& w,
                                 double* e_coul, double* e_gb, T* force, T* dEdq, T* dEdrho,
-                                hipStream_t s, hipEvent_t* ev, bool staged)
+                                hipStream_t s, hipEvent_t* ev, bool staged, bool finalize, T* born_R)
 {
     const bool grad = force || dEdq || dEdrho;
     const bool chain = force || dEdrho;
@@ -3190,7 +3224,8 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
                                       sk, ck, w))
 #define GBMC_ENERGY_WIDE(G_, S_)                                                                 \
     GBMC_LAUNCH_TIMED(ev, kKEnergy, (k_energy_wide<T, G_, S_>), dim3(pe.n_items),                   \
-                      dim3(kWideEnergy * kTile), s, pe.items, w.P, (T)c.kC, (T)c.kT, sk, w)
+                      dim3(kWideEnergy * kTile), s, pe.items, w.P, (T)c.kC, (T)c.kT, sk, w, finalize,  \
+                      c, born_R)
         const bool salt = c.kappa != 0.0, cut = c.cutoff > 0.0, one = pe.one_tile;
         if (pe.wide && !cut) {
             if (grad) {
@@ -3232,6 +3267,8 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
     if (!chain && n_sum + n_fin > 0)
         hipLaunchKernelGGL(k_energy_finalize<T>, dim3(n_sum + n_fin), dim3(256), 0, s, n_atoms, sums,
                            n_sum, w, e_coul, e_gb, dEdq, grad);
+    const PostOut<T> po{sums, n_sum, e_coul, e_gb, dEdq, force, dEdrho, c.offset};
+    const bool late_post = pc.n_items > 0 && pc.wide && c.rgbmax <= 0.0;
     if (chain && pc.n_items > 0) {
         if (c.rgbmax > 0.0)
             GBMC_DISPATCH_W(pc.waves_per_group,
@@ -3240,8 +3277,9 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
                                               pc.items, pc.n_items, w.P, w.Gx, w,
                                               (T)c.rgbmax))
         else if (pc.wide)
-            GBMC_LAUNCH_TIMED(ev, kKChain, k_chain_wide<T>, dim3(pc.n_items), dim3(kWide * kTile), s,
-                              pc.items, w.P, w.Gx, w);
+            GBMC_LAUNCH_TIMED(ev, kKChain, k_chain_wide<T>, dim3(pc.n_items + n_sum),
+                              dim3(kWide * kTile), s, pc.items, pc.n_items, w.P, w.Gx, w, po, pc.total,
+                              w.qcnt + 2 * (size_t)cp.n_blocks);
         else if (pc.one_tile)
             GBMC_DISPATCH_W(pc.waves_per_group,
                             GBMC_LAUNCH_TIMED(ev, kKChain, (k_chain_pairs<T, W, false, true>),
@@ -3253,9 +3291,9 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
                                               dim3(blocks_for(pc.n_items, W)), dim3(kTile * W), s,
                                               pc.items, pc.n_items, w.P, w.Gx, w, (T)0))
     }
-    if (chain && n_sum + n_fin > 0)
-        hipLaunchKernelGGL(k_post<T>, dim3(n_sum + n_fin), dim3(256), 0, s, n_atoms, sums, n_sum, w,
-                           e_coul, e_gb, dEdq, force, dEdrho, rho, c.offset);
+    // (the wide chain pass wrote every output itself)
+    if (chain && !late_post && n_sum + n_fin > 0)
+        hipLaunchKernelGGL(k_post<T>, dim3(n_sum + n_fin), dim3(256), 0, s, n_atoms, po, w);
     return hipGetLastError();
 }
 
@@ -3270,7 +3308,7 @@ static hipError_t queued_dispatch(const PQueue& pq, int ntot, const QueueShape& 
     auto kern = k_pairs_queue<T, kPersistW, P0, P1, G, S, O>;
     const SaltK<T> sk{(T)c.kO, (T)c.kappa, (T)(c.kappa * kLog2e)};
     GBMC_LAUNCH_TIMED(ev, id, kern, dim3(blocks_for(ntot, kPersistW)), dim3(kTile * kPersistW), s,
-                      pq, rho, c, (T)c.kC, (T)c.kT, sk, w, born_R);
+                      pq, c, (T)c.kC, (T)c.kT, sk, w, born_R);
     return hipGetLastError();
 }
 
@@ -3325,8 +3363,8 @@ hipError_t launch_queued(const QueueShape& sh, int n_atoms, const SumSpan* sums,
     const int n_sum = (e_coul || e_gb) ? n_sums : 0;
     const int n_fin = (force || dEdq || dEdrho) ? blocks_for(n_atoms, 256) : 0;
     if (n_sum + n_fin > 0)
-        hipLaunchKernelGGL(k_post<T>, dim3(n_sum + n_fin), dim3(256), 0, s, n_atoms, sums, n_sum, w,
-                           e_coul, e_gb, dEdq, force, dEdrho, rho, c.offset);
+        hipLaunchKernelGGL(k_post<T>, dim3(n_sum + n_fin), dim3(256), 0, s, n_atoms,
+                           (PostOut<T>{sums, n_sum, e_coul, e_gb, dEdq, force, dEdrho, c.offset}), w);
     return hipGetLastError();
 }
 
@@ -3405,13 +3443,13 @@ hipError_t launch_remd_exchange(int M, const double* E_rung, const int32_t* Ne, 
                                         const T*,                                                \
                                         const T*, const T*, const T*, const T*, const GBConst&,  \
                                         const Work<T>&, T*, hipStream_t, hipEvent_t*,            \
-                                        const T*);                                               \
+                                        const T*, bool);                                         \
     template hipError_t launch_energy_forces<T>(const PassShape&, const PassShape&, int,           \
                                                 const SumSpan*, int, const CutPlan&, const T*,     \
                                                 const T*, const T*, const T*, const T*,          \
                                                 const T*, const GBConst&, const Work<T>&,        \
                                                 double*, double*, T*, T*, T*, hipStream_t,       \
-                                                hipEvent_t*, bool);                              \
+                                                hipEvent_t*, bool, bool, T*);                    \
     template hipError_t launch_queued<T>(const QueueShape&, int, const SumSpan*, int, const T*, const T*,       \
                                          const T*, const T*, const T*, const T*, const GBConst&, \
                                          const Work<T>&, T*, double*, double*, T*, T*, T*,       \

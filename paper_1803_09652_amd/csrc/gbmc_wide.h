@@ -15,6 +15,14 @@
 // a launch that fills the chip keeps the walk (wide_items in gbmc_host.cpp).
 // 256 atoms: descreening 13.5 -> 8.4 us, energy 15.0 -> 9.1, chain 25.9 -> 12.4.
 
+// Two launches of an evaluation drop out as well: the energy pass of gb_evaluate forms
+// the Born radii of its atoms itself (radius_state, once per workgroup and block;
+// 3.1 us for the launch, under 1 us here), and the chain pass writes the
+// outputs.  256 atoms, a whole evaluation: 41.5 -> 37.9 -> 36.7 us; 3,001 atoms
+// (only the chain pass runs wide): 72.3 -> 71.7.  A launch that fills the
+// chip keeps both kernels: there forming a radius in every item costs more
+// FP64 issue (a tanh and four divisions per lane) than the launch.
+
 // Wavefronts per workgroup.  The energy pass has most sums to share out and
 // runs wide only where every workgroup has a CU of its own: there 16 took 9.5 us
 // and 8 took 12.5 on 16 systems of 237 atoms.  In the other passes 16 gained
@@ -248,7 +256,8 @@ struct EnergyWide {
 template <typename T, bool GRAD, int R, bool SALT, int NT>
 __device__ __forceinline__ void energy_wide(EnergyWide<T, NT>& L, const WorkItem& w, int wave,
                                             int lane, const Q4<T>* __restrict__ P, T kC, T kT,
-                                            const SaltK<T>& sk, const Work<T>& wk)
+                                            const SaltK<T>& sk, const Work<T>& wk, bool finalize,
+                                            const GBConst& gc, T* __restrict__ born_R)
 {
     constexpr int FR = GRAD ? 3 : 0, CG = GRAD ? 4 : 0;     // terms of the gradients
     const int J = w.J0, j = J * kTile + lane;
@@ -261,7 +270,14 @@ __device__ __forceinline__ void energy_wide(EnergyWide<T, NT>& L, const WorkItem
             const int g = w.base + a;
             const Q4<T> p = P[g];
             v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w * ek.sq;
-            v[4] = wk.R_t[g]; v[5] = wk.a_t[g];
+            // (finalize: the radii are formed here, and stored by the diagonal item)
+            if (finalize) {
+                const RadiusState st = radius_state(wk.I_fx[g], (double)wk.Gx[g].w, gc);
+                v[4] = (T)st.R; v[5] = (T)(kAScale / st.R);
+                if (diagonal && wave == 0) radius_store<T>(g, wk.perm[g], st, p, wk, born_R);
+            } else {
+                v[4] = wk.R_t[g]; v[5] = wk.a_t[g];
+            }
         } else {
             dummy_pos(a, v[0], v[1], v[2]);
             v[3] = T(0); v[4] = T(1); v[5] = T(kAScale);
@@ -411,16 +427,20 @@ __device__ __forceinline__ void energy_wide(EnergyWide<T, NT>& L, const WorkItem
 template <typename T, bool GRAD, bool SALT>
 __global__ __launch_bounds__(kWideEnergy * kTile) void k_energy_wide(const WorkItem* __restrict__ items,
                                                               const Q4<T>* __restrict__ P, T kC,
-                                                              T kT, SaltK<T> sk, Work<T> wk)
+                                                              T kT, SaltK<T> sk, Work<T> wk,
+                                                              bool finalize, GBConst gc,
+                                                              T* __restrict__ born_R)
 {
     constexpr int NT = (GRAD ? 5 : 3) + (SALT ? 1 : 0);
     __shared__ EnergyWide<T, NT> L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kTile), lane = threadIdx.x % kTile;
     const WorkItem w = items[blockIdx.x];
     if (sizeof(T) == 4 && w.rows == 2)
-        energy_wide<T, GRAD, sizeof(T) == 4 ? 2 : 1, SALT, NT>(L, w, wave, lane, P, kC, kT, sk, wk);
+        energy_wide<T, GRAD, sizeof(T) == 4 ? 2 : 1, SALT, NT>(L, w, wave, lane, P, kC, kT, sk, wk, finalize,
+                                                               gc, born_R);
     else
-        energy_wide<T, GRAD, 1, SALT, NT>(L, w, wave, lane, P, kC, kT, sk, wk);
+        energy_wide<T, GRAD, 1, SALT, NT>(L, w, wave, lane, P, kC, kT, sk, wk, finalize,
+                                                               gc, born_R);
 }
 
 // -------------------------------------------------------- Born-radius chain
@@ -516,7 +536,8 @@ __device__ __forceinline__ void chain_wide_walk(ChainWide<T>& L, int wave, int l
 template <typename T, int R>
 __device__ __forceinline__ void chain_wide(ChainWide<T>& L, const WorkItem& w, int wave, int lane,
                                            const Q4<T>* __restrict__ P, const Q4<T>* __restrict__ Gx,
-                                           const Work<T>& wk)
+                                           const Work<T>& wk, const PostOut<T>& po,
+                                           const int* __restrict__ total, int* __restrict__ cnt)
 {
     const int J = w.J0, j = J * kTile + lane;
     const bool diagonal = R == 1 && J == w.I;
@@ -602,18 +623,39 @@ __device__ __forceinline__ void chain_wide(ChainWide<T>& L, const WorkItem& w, i
         if (a < w.n) fx_add(&out[w.base + a], f);
     }
     if (bad) *wk.ovf = 1;
+    // The workgroup whose sums are a block's last writes that block's outputs (a
+    // launch of their own took 3.8 us of a 38 us evaluation of 256 atoms).  vmcnt(0):
+    // every sum of the workgroup is added before it is counted.
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    __syncthreads();
+    const int X = wave == 0 ? J : w.I + wave - 1;
+    if (wave > R || (diagonal && wave == 1)) return;
+    int before = 0;
+    if (lane == 0) before = atomicAdd(cnt + w.blk0 + X, 1);
+    if (__builtin_amdgcn_readfirstlane(before) != total[w.blk0 + X] - 1) return;
+    if (X * kTile + lane < w.n) post_atom<T, true>(w.base + X * kTile + lane, po, wk);
 }
 
+// Workgroups [0, n_items) take one work item each; the following ones sum the
+// energy shares, final before this pass begins.  total: the items that touch each
+// block; cnt: those counted so far (cleared by the staging kernel).
 template <typename T>
 __global__ __launch_bounds__(kWide * kTile) void k_chain_wide(const WorkItem* __restrict__ items,
-                                                             const Q4<T>* __restrict__ P,
-                                                             const Q4<T>* __restrict__ Gx, Work<T> wk)
+                                                             int n_items, const Q4<T>* __restrict__ P,
+                                                             const Q4<T>* __restrict__ Gx, Work<T> wk,
+                                                             PostOut<T> po,
+                                                             const int* __restrict__ total,
+                                                             int* __restrict__ cnt)
 {
     __shared__ ChainWide<T> L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kTile), lane = threadIdx.x % kTile;
+    if ((int)blockIdx.x >= n_items) {
+        if (threadIdx.x < 256) sum_energies<T>(po.sums[blockIdx.x - n_items], wk, po.e_coul, po.e_gb);
+        return;
+    }
     const WorkItem w = items[blockIdx.x];
     if (sizeof(T) == 4 && w.rows == 2)
-        chain_wide<T, sizeof(T) == 4 ? 2 : 1>(L, w, wave, lane, P, Gx, wk);
+        chain_wide<T, sizeof(T) == 4 ? 2 : 1>(L, w, wave, lane, P, Gx, wk, po, total, cnt);
     else
-        chain_wide<T, 1>(L, w, wave, lane, P, Gx, wk);
+        chain_wide<T, 1>(L, w, wave, lane, P, Gx, wk, po, total, cnt);
 }
