@@ -101,6 +101,8 @@ class Plan:
     precision: "fp32" (FP32 pair arithmetic, 64-bit fixed-point sums) or
     "fp64".  Owns the plan's device workspace."""
 
+    single_launch = False       # see set_single_launch
+
     def __init__(self, atom_offset: Sequence[int], precision: str = "fp32",
                  j_blocks_per_item=None, waves_per_group=None, device=None):
         lib = L.load()
@@ -156,6 +158,7 @@ class Plan:
         bounded dependency waits of wait_polls polls; 0 gives up at once, for
         tests) instead of one launch per pass (the default, faster here)."""
         L.check(L.load().gbmc_plan_set_single_launch(self._h, int(bool(enable)), int(wait_polls)))
+        self.single_launch = bool(enable)
 
     def set_timing(self, enable: bool = True) -> None:
         """Time each hot-path kernel of later eager calls (HIP events bound to
@@ -490,14 +493,7 @@ def plain_fp64(atom_offset, x, y, z, q, rho, screen, params: GBParams = IGB5,
     return out
 
 
-def md_step(plan: Plan, atoms: Atoms, v: torch.Tensor, force: torch.Tensor,
-            inv_mass: torch.Tensor, xi: torch.Tensor, dt: float, gamma: float, T: float = 300.0,
-            xref: Optional[torch.Tensor] = None, k_restr: float = 0.0) -> None:
-    """One leapfrog Langevin step (Loncharich, Brooks & Pastor 1992) of every
-    atom: atoms.x/y/z and v [3, N] (A/ps) are updated in place from force
-    [N, 3] (kcal/mol/A, e.g. energy_forces()["force"]), inv_mass [N] (1/amu),
-    standard normals xi [3, N] and an optional harmonic restraint to xref
-    [3, N] (k_restr kcal/mol/A^2); dt in ps, gamma in 1/ps."""
+def _md_check(plan: Plan, v, force, inv_mass, xi, xref) -> None:
     n, dt_ = plan.n_atoms, plan.dtype
 
     def chk(t, shape, name):
@@ -509,6 +505,17 @@ def md_step(plan: Plan, atoms: Atoms, v: torch.Tensor, force: torch.Tensor,
     chk(xi, (3, n), "xi")
     if xref is not None:
         chk(xref, (3, n), "xref")
+
+
+def md_step(plan: Plan, atoms: Atoms, v: torch.Tensor, force: torch.Tensor,
+            inv_mass: torch.Tensor, xi: torch.Tensor, dt: float, gamma: float, T: float = 300.0,
+            xref: Optional[torch.Tensor] = None, k_restr: float = 0.0) -> None:
+    """One leapfrog Langevin step (Loncharich, Brooks & Pastor 1992) of every
+    atom: atoms.x/y/z and v [3, N] (A/ps) are updated in place from force
+    [N, 3] (kcal/mol/A, e.g. energy_forces()["force"]), inv_mass [N] (1/amu),
+    standard normals xi [3, N] and an optional harmonic restraint to xref
+    [3, N] (k_restr kcal/mol/A^2); dt in ps, gamma in 1/ps."""
+    _md_check(plan, v, force, inv_mass, xi, xref)
     L.check(L.load().md_langevin_step(plan.handle, _ptr(atoms.x), _ptr(atoms.y), _ptr(atoms.z),
                                       _ptr(v), _ptr(force), _ptr(inv_mass), _ptr(xi), _ptr(xref),
                                       float(k_restr), float(dt), float(gamma), float(T),

@@ -10,6 +10,7 @@ Every step is a fixed sequence of library calls on the current stream:
     gb_radii -> [mc_state_dE -> mc_step] -> [remd_exchange]
              -> gb_energy_forces (forces) -> md_langevin_step
 
+(gb_evaluate in place of the two on the steps without an attempt),
 so an attempt is made at the coordinates the dynamics halted at, and the
 charges it leaves drive the dynamics from that point on (Fig. 1).  The loop itself
 does no arithmetic: it picks the calls and the random inputs (Langevin noise
@@ -26,11 +27,13 @@ their redox potentials, section III.B): `ladders` lists the rung ranges
 """
 from __future__ import annotations
 
+import ctypes as C
 from typing import Optional
 
 import numpy as np
 import torch
 
+from . import _lib as L
 from . import api
 
 
@@ -130,10 +133,31 @@ class ReplicaMD:
                "rep_of_rung": torch.empty((len(att), B), dtype=torch.int32, device=dev),
                "n_electrons": torch.empty((len(att), B), dtype=torch.int32, device=dev)}
         noise = torch.empty((3, N), dtype=plan.dtype, device=dev)
+        # the call's buffers and argument lists, built once: a step is then a few
+        # library calls, 20 us of host time for 47 with the per-call wrappers (16 x 237
+        # atoms, where the host bounds the loop)
+        out = api._eval_outputs(plan, True, False, False)
+        f = out["force"]
+        noises = [noise] * n_steps if xi is None else xi.unbind(0)
+        if n_steps > 0:
+            api._md_check(plan, self.v, f, self.inv_mass, noises[0], self.xref)
+        lib, ptr, stream = L.load(), api._ptr, api._stream(dev)
+        atoms_c, params_c = self.atoms.c(), self.params.c()
+        gb_in = (plan.handle, C.byref(atoms_c), C.byref(params_c), ptr(plan.workspace))
+        gb_out = (ptr(out["e_coul"]), ptr(out["e_gb"]), ptr(f), None, None, stream)
+        R = ptr(out["R"])
+        md_in = (plan.handle, ptr(self.atoms.x), ptr(self.atoms.y), ptr(self.atoms.z), ptr(self.v),
+                 ptr(f), ptr(self.inv_mass))
+        md_par = (ptr(self.xref), self.k_restr, self.dt, self.gamma, self.T, stream)
         a_i = x_i = 0
         for k in range(k0, k0 + n_steps):
-            api.radii(plan, self.atoms, self.params)
-            if self.attempt_every and (k + 1) % self.attempt_every == 0:
+            # an attempt changes charges between the radii and the forces; without one
+            # both are a single evaluation, which stages the atoms once (and, in small
+            # plans, forms the radii in the energy pass): two to three launches fewer of eight
+            attempt = self.attempt_every and (k + 1) % self.attempt_every == 0
+            split = attempt or plan.single_launch
+            L.check(lib.gb_radii(*gb_in, R, stream) if split else lib.gb_evaluate(*gb_in, R, *gb_out))
+            if attempt:
                 u = u_mc[a_i] if u_mc is not None else \
                     torch.rand((B, 6), dtype=torch.float64, device=dev, generator=self.gen)
                 dE, dG = api.mc_state_dE(plan, self.sites, self.atoms, self.state, self.pH,
@@ -168,13 +192,11 @@ class ReplicaMD:
                     self._acc_x += acc.sum()
                 x_i += 1
                 self.n_exchanges += 1
-            f = api.energy_forces(plan, self.atoms, self.params, dEdq=False, dEdrho=False)["force"]
-            if xi is not None:
-                noise = xi[k - k0]
-            else:
+            if split:
+                L.check(lib.gb_energy_forces(*gb_in, *gb_out))
+            if xi is None:
                 torch.randn((3, N), dtype=plan.dtype, device=dev, generator=self.gen, out=noise)
-            api.md_step(plan, self.atoms, self.v, f, self.inv_mass, noise, self.dt, self.gamma,
-                        self.T, xref=self.xref, k_restr=self.k_restr)
+            L.check(lib.md_langevin_step(*md_in, ptr(noises[k - k0]), *md_par))
         self.step_index = k0 + n_steps
         return rec
 
