@@ -107,8 +107,8 @@ struct gbmc_plan {
     int64_t n_rec[kNumKernels] = {};
     hipEvent_t cur[2 * kNumKernels] = {};
     // workspace layout (byte offsets)
-    size_t off_I, off_F, off_G, off_phi, off_drho, off_EA, off_I64, off_R64, off_T64, off_dR64, off_dRp,
-        off_Rt, off_at, off_ovf, off_q, off_P, off_Gx, off_A64, off_rows, off_bnd,
+    size_t off_I, off_F, off_G, off_phi, off_drho, off_EA, off_dRp,
+        off_Rt, off_at, off_ovf, off_q, off_P, off_Gx, off_rows, off_bnd,
         off_smax, off_box, off_cit0, off_cit1, off_ccount, ws_bytes;
     int32_t cut_cap = 0;             // capacity of each compacted cutoff work list
 };
@@ -249,12 +249,7 @@ static Work<T> carve(const gbmc_plan* p, void* ws)
     w.phi_fx = reinterpret_cast<unsigned long long*>(b + p->off_phi);
     w.drho_fx = reinterpret_cast<unsigned long long*>(b + p->off_drho);
     w.EA_fx = reinterpret_cast<unsigned long long*>(b + p->off_EA);
-    w.I64 = reinterpret_cast<double*>(b + p->off_I64);
-    w.R64 = reinterpret_cast<double*>(b + p->off_R64);
-    w.A64 = reinterpret_cast<double*>(b + p->off_A64);
     w.rows = reinterpret_cast<Row64*>(b + p->off_rows);
-    w.T64 = reinterpret_cast<double*>(b + p->off_T64);
-    w.dRdPsi64 = reinterpret_cast<double*>(b + p->off_dR64);
     w.dRdPsi_p = reinterpret_cast<double*>(b + p->off_dRp);
     w.R_t = reinterpret_cast<T*>(b + p->off_Rt);
     w.a_t = reinterpret_cast<T*>(b + p->off_at);
@@ -287,11 +282,6 @@ static void layout(gbmc_plan* p)
     p->off_drho = p->off_phi + 8 * N;
     p->off_EA = p->off_drho + 8 * N;
     (void)B;
-    p->off_I64 = seg(8 * N);
-    p->off_R64 = seg(8 * N);
-    p->off_A64 = seg(8 * N);
-    p->off_T64 = seg(8 * N);
-    p->off_dR64 = seg(8 * N);
     p->off_dRp = seg(8 * N);
     p->off_Rt = seg(ts * N);
     p->off_at = seg(ts * N);

@@ -1515,33 +1515,40 @@ __device__ __forceinline__ RadiusState radius_state(unsigned long long I_fx, dou
 }
 
 // Stores the state of atom k (processing order), which is atom g of the caller.
-template <typename T>
+// (All of the atom's loads come before its stores: a load waits for every store
+// issued before it.)
+template <typename T, bool QUEUED>
 __device__ __forceinline__ void radius_store(int k, int g, const RadiusState& st, const Q4<T>& p,
                                              const Work<T>& w, T* __restrict__ born_R)
 {
-    w.I64[g] = st.I;
-    w.R64[g] = st.R;
-    w.A64[g] = 0.5 / st.R;
-    w.T64[g] = st.t;
-    st_dev(w.dRdPsi64 + g, st.dRdPsi);
-    st_dev(w.dRdPsi_p + k, st.dRdPsi);
-    st_dev(w.R_t + k, (T)st.R);
-    st_dev(w.a_t + k, (T)(kAScale / st.R));
-    // FP64 record of the atom for the Monte Carlo kernels (caller order)
+    if constexpr (QUEUED) {
+        st_dev(w.dRdPsi_p + k, st.dRdPsi);
+        st_dev(w.R_t + k, (T)st.R);
+        st_dev(w.a_t + k, (T)(kAScale / st.R));
+    } else {
+        w.dRdPsi_p[k] = st.dRdPsi;
+        w.R_t[k] = (T)st.R;
+        w.a_t[k] = (T)(kAScale / st.R);
+    }
+    // FP64 record of the atom (caller order), written whole
     Row64 row;
     row.x = (double)p.x; row.y = (double)p.y; row.z = (double)p.z;
     row.R = st.R; row.A = 0.5 / st.R;
-    row.pad0 = row.pad1 = row.pad2 = 0.0;
+    row.I = st.I; row.t = st.t; row.dRdPsi = st.dRdPsi;
     w.rows[g] = row;
     if (born_R) born_R[g] = (T)st.R;
 }
 
-template <typename T>
+// QUEUED: other items of the same launch read the sum's parts and the state.
+template <typename T, bool QUEUED>
 __device__ __forceinline__ void radii_final_atom(int k, const GBConst& c, const Work<T>& w,
                                                  T* __restrict__ born_R)
 {
-    const RadiusState st = radius_state(ld_dev(w.I_fx + k), (double)w.Gx[k].w, c);
-    radius_store<T>(k, w.perm[k], st, w.P[k], w, born_R);
+    const int g = w.perm[k];
+    const Q4<T> p = w.P[k];
+    const T rho = w.Gx[k].w;
+    const RadiusState st = radius_state(QUEUED ? ld_dev(w.I_fx + k) : w.I_fx[k], (double)rho, c);
+    radius_store<T, QUEUED>(k, g, st, p, w, born_R);
 }
 
 template <typename T>
@@ -1549,7 +1556,7 @@ __global__ void k_radii_finalize(int n_atoms, GBConst c, Work<T> w, T* __restric
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n_atoms) return;
-    radii_final_atom<T>(k, c, w, born_R);
+    radii_final_atom<T, false>(k, c, w, born_R);
 }
 
 // ================================================================ pass 2
@@ -1878,8 +1885,8 @@ __global__ __launch_bounds__(kTile * W) void k_energy_pairs(
 // each adds its two sums to the system's in qcnt (cleared by the staging
 // kernel) and the last to arrive writes: integer sums, so the order does not
 // matter.  One workgroup per system read a 100,000-atom system's shares at
-// 14 GB/s, in 116 us; spans of 4,096 atoms (sixteen loads in flight per thread)
-// take the whole kernel to 8 us.
+// 14 GB/s, in 116 us; spans of 4,096 atoms, with all of a thread's 32 loads in
+// flight, take the whole kernel to 5 us (one load after the other: 8).
 template <typename T>
 __device__ __forceinline__ void sum_energies(const SumSpan sp, const Work<T>& w,
                                              double* __restrict__ e_coul, double* __restrict__ e_gb)
@@ -1888,13 +1895,20 @@ __device__ __forceinline__ void sum_energies(const SumSpan sp, const Work<T>& w,
     const int t = threadIdx.x, lane = t % kTile, wave = t / kTile;
     long long s0 = 0, s1 = 0;
     for (int g0 = sp.a0; g0 < sp.a1; g0 += kSumAtoms) {
+        // (every thread loads, past the end the last atom's shares, and then selects:
+        // a load inside a branch would wait before the next one is issued)
+        long long v[kSumAtoms / 256][2];
 #pragma unroll
         for (int u = 0; u < kSumAtoms / 256; ++u) {
-            const int g = g0 + u * 256 + t;
-            if (g < sp.a1) {
-                s0 += (long long)w.EA_fx[g];
-                s1 += (long long)w.EA_fx[w.n_atoms + g];
-            }
+            const int g = min(g0 + u * 256 + t, sp.a1 - 1);
+            v[u][0] = (long long)w.EA_fx[g];
+            v[u][1] = (long long)w.EA_fx[w.n_atoms + g];
+        }
+#pragma unroll
+        for (int u = 0; u < kSumAtoms / 256; ++u) {
+            const bool in = g0 + u * 256 + t < sp.a1;
+            s0 += in ? v[u][0] : 0;
+            s1 += in ? v[u][1] : 0;
         }
     }
 #pragma unroll
@@ -2280,24 +2294,30 @@ __device__ __forceinline__ void post_atom(int k, const PostOut<T>& o, const Work
     auto sum = [&](const unsigned long long* p) {
         return (double)(long long)(LATE ? ld_dev(p) : *p) * (1.0 / kScaleF);
     };
+    // all loads first: a load waits for every store issued before it
     const int g = w.perm[k];
-    if (o.dEdq) o.dEdq[g] = (T)((double)(long long)w.phi_fx[k] * (1.0 / kScaleF));
+    double phi = 0.0, f[3] = {0.0, 0.0, 0.0}, v = 0.0;
+    if (o.dEdq) phi = (double)(long long)w.phi_fx[k] * (1.0 / kScaleF);
     if (o.force) {
 #pragma unroll
-        for (int a = 0; a < 3; ++a)
-            o.force[3 * (size_t)g + a] = (T)sum(w.F_fx + (size_t)a * w.n_atoms + k);
+        for (int a = 0; a < 3; ++a) f[a] = sum(w.F_fx + (size_t)a * w.n_atoms + k);
     }
     if (o.dEdrho) {
         const double rho = (double)w.Gx[k].w;
         const double rt = rho - o.offset;
-        const double R = w.R64[g];
+        const Row64 r = w.rows[g];
         // G = dE/dR from its fixed-point sum and the chain weight B = G dR/dPsi
         const double G = (double)(long long)w.G_fx[k] * (1.0 / kScaleF);
-        const double B = G * w.dRdPsi64[g];
-        const double v = fma(G * R * R, 1.0 / (rt * rt) - w.T64[g] / (rho * rho), B * w.I64[g]) +
-                         sum(w.drho_fx + k);
-        o.dEdrho[g] = (T)v;
+        const double B = G * r.dRdPsi;
+        v = fma(G * r.R * r.R, 1.0 / (rt * rt) - r.t / (rho * rho), B * r.I) +
+            sum(w.drho_fx + k);
     }
+    if (o.dEdq) o.dEdq[g] = (T)phi;
+    if (o.force) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) o.force[3 * (size_t)g + a] = (T)f[a];
+    }
+    if (o.dEdrho) o.dEdrho[g] = (T)v;
 }
 
 // (All-pairs FP32: the waves per SIMD that the walk needs, 5 for single-tile and 4
@@ -2496,7 +2516,7 @@ __global__ __launch_bounds__(kTile * W) void k_pairs_queue(
                                 T(0), wk.box);
         pq_complete(q, 0, w, lane, [&](int L) {
             const int i = L * kTile + lane;
-            if (i < w.n) radii_final_atom<T>(w.base + i, c, wk, born_R);
+            if (i < w.n) radii_final_atom<T, true>(w.base + i, c, wk, born_R);
         });
     } else if (P0 <= 1 && P1 >= 1 && p == 1) {
         const CutK<T> ck{T(0), T(0)};
@@ -2675,7 +2695,7 @@ constexpr int kSDE = 256;
 template <typename T>
 __global__ __launch_bounds__(kSDE) void k_site_dE(
     SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
-    const T* __restrict__ Q, const double* __restrict__ R64, const double* __restrict__ A64,
+    const T* __restrict__ Q, const Row64* __restrict__ rows,
     double kC, double kT, double kO, double kap, double cut2,
     const unsigned long long* __restrict__ phi_fx,
     const int32_t* __restrict__ current_state,
@@ -2699,8 +2719,8 @@ __global__ __launch_bounds__(kSDE) void k_site_dE(
     const double* qcur = sd.state_charges + sd.state_charge_offset[g0 + cur];
     for (int a = t; a < na; a += kSDE) {
         int g = sd.site_atoms[a0 + a];
-        double R = R64[g];
-        sx[a] = X[g]; sy[a] = Y[g]; sz[a] = Z[g]; sR[a] = R; sA[a] = A64[g];
+        const double R = rows[g].R;
+        sx[a] = X[g]; sy[a] = Y[g]; sz[a] = Z[g]; sR[a] = R; sA[a] = rows[g].A;
         double phi = -gb_kd(R, kC, kT, kO, kap) * (double)Q[g] / R;   // self term
         phi += (double)(long long)phi_fx[sa_site0 + a] * (1.0 / kScaleP);
         sphi[a] = phi;
@@ -2764,7 +2784,7 @@ __device__ __forceinline__ int pick_index(double u, int n)
 template <typename T>
 __global__ __launch_bounds__(kMC) void k_mc_step(
     SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
-    T* __restrict__ Q, const double* __restrict__ R64, const double* __restrict__ A64, double kC,
+    T* __restrict__ Q, const Row64* __restrict__ rows, double kC,
     double kT, double kO, double kap, double cut2, int32_t* __restrict__ current_state,
     const double* __restrict__ pH,
     const double* __restrict__ E_volt, double T_kelvin, const double* __restrict__ dEin,
@@ -2818,8 +2838,8 @@ __global__ __launch_bounds__(kMC) void k_mc_step(
                     int a = p / nap, c = p - a * nap;
                     int ga = sd.site_atoms[ar0 + a], gc = sd.site_atoms[ap0 + c];
                     double K = pairK((double)X[ga] - (double)X[gc], (double)Y[ga] - (double)Y[gc],
-                                     (double)Z[ga] - (double)Z[gc], R64[ga], A64[ga], R64[gc],
-                                     A64[gc], kC, kT, kO, kap, cut2);
+                                     (double)Z[ga] - (double)Z[gc], rows[ga].R, rows[ga].A,
+                                     rows[gc].R, rows[gc].A, kC, kT, kO, kap, cut2);
                     part[0] += (qr1[a] - qr0[a]) * (qp1[c] - qp0[c]) * K;
                 }
                 block_sum<1, kMC / kTile>(red, part);
@@ -2889,7 +2909,7 @@ constexpr int kCouple = 512;    // threads per pair of sites
 template <typename T>
 __global__ __launch_bounds__(kCouple) void k_site_couple(
     SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
-    const T* __restrict__ Q, const double* __restrict__ R64, const double* __restrict__ A64, double kC,
+    const T* __restrict__ Q, const Row64* __restrict__ rows, double kC,
     double kT, double kO, double kap, double cut2, const unsigned long long* __restrict__ phi_fx,
     const int32_t* __restrict__ current_state, int kinds, const double* __restrict__ u,
     double* __restrict__ couple)
@@ -2916,9 +2936,9 @@ __global__ __launch_bounds__(kCouple) void k_site_couple(
         const double* qn = sd.state_charges + sd.state_charge_offset[g0 + sweep_proposal(sd, m[h], s, u)];
         const double* qo = sd.state_charges + sd.state_charge_offset[g0 + s];
         const int g = sd.site_atoms[a0[h] + a];
-        const double R = R64[g], dq = qn[a] - qo[a];
+        const double R = rows[g].R, dq = qn[a] - qo[a];
         sx[h][a] = X[g]; sy[h][a] = Y[g]; sz[h][a] = Z[g];
-        sR[h][a] = R; sA[h][a] = A64[g];
+        sR[h][a] = R; sA[h][a] = rows[g].A;
         sdq[h][a] = dq;
         if (same && h == 0) {
             const double k = gb_kd(R, kC, kT, kO, kap) / R;
@@ -3202,7 +3222,9 @@ hipError_t launch_energy_forces(const PassShape& pe, const PassShape& pc, int n_
     // alongside (staged: the full evaluation's radii staging did both)
     if (n_atoms > 0 && !staged) {
         StageClear zc{};
-        zc.acc0 = w.F_fx; zc.n_acc0 = 8;
+        // energies alone add to the last two of the eight accumulators
+        zc.acc0 = grad ? w.F_fx : w.EA_fx;
+        zc.n_acc0 = grad ? 8 : 2;
         zc.cnt = w.qcnt; zc.n_cnt = 3 * cp.n_blocks;
         hipLaunchKernelGGL(k_stage<T>, dim3(blocks_for(cp.n_blocks, 4)), dim3(256), 0, s,
                            cp.blocks, cp.n_blocks, n_atoms, w.perm, x, y, z, q, rho, screen,
@@ -3382,7 +3404,7 @@ hipError_t launch_state_dE(const SiteDev& sd, int n_atoms, const T* x, const T* 
         GBMC_LAUNCH_TIMED(ev, kKSiteRows, rows, dim3(sd.n_rowitems), dim3(kTile), s, sd.rowitems, sd.site_atoms, w.rows, q, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, w.ovf);
     }
     GBMC_LAUNCH_TIMED(ev, kKSiteDE, k_site_dE<T>, dim3(sd.n_sites), dim3(kSDE), s, sd, x, y, z, q,
-                      w.R64, w.A64, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state, pH, E_volt, T_kelvin, dE,
+                      w.rows, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state, pH, E_volt, T_kelvin, dE,
                       dG);
     return hipGetLastError();
 }
@@ -3396,8 +3418,7 @@ hipError_t launch_mc_step(const SiteDev& sd, int n_sys, const T* x, const T* y, 
                           hipStream_t s, hipEvent_t* ev)
 {
     if (n_sys == 0) return hipSuccess;
-    GBMC_LAUNCH_TIMED(ev, kKMCStep, k_mc_step<T>, dim3(n_sys), dim3(kMC), s, sd, x, y, z, q, w.R64,
-                      w.A64, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), current_state, pH, E_volt, T_kelvin, dE, dG, u, n_electrons,
+    GBMC_LAUNCH_TIMED(ev, kKMCStep, k_mc_step<T>, dim3(n_sys), dim3(kMC), s, sd, x, y, z, q, w.rows, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), current_state, pH, E_volt, T_kelvin, dE, dG, u, n_electrons,
                       counters, accepted);
     return hipGetLastError();
 }
@@ -3419,7 +3440,7 @@ hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, const T*
     }
     if (sd.n_couples > 0)
         hipLaunchKernelGGL(k_site_couple<T>, dim3(sd.n_couples), dim3(kCouple), 0, s, sd, x, y, z, q,
-                           w.R64, w.A64, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state,
+                           w.rows, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state,
                            kinds, u, couple);
     const size_t cached = (size_t)std::min(max_sites, kSweepCache);
     hipLaunchKernelGGL(k_mc_sweep<T>, dim3(n_sys), dim3(kSweep), sizeof(double) * cached * cached, s, sd,

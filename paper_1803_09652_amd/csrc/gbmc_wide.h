@@ -274,7 +274,7 @@ __device__ __forceinline__ void energy_wide(EnergyWide<T, NT>& L, const WorkItem
             if (finalize) {
                 const RadiusState st = radius_state(wk.I_fx[g], (double)wk.Gx[g].w, gc);
                 v[4] = (T)st.R; v[5] = (T)(kAScale / st.R);
-                if (diagonal && wave == 0) radius_store<T>(g, wk.perm[g], st, p, wk, born_R);
+                if (diagonal && wave == 0) radius_store<T, false>(g, wk.perm[g], st, p, wk, born_R);
             } else {
                 v[4] = wk.R_t[g]; v[5] = wk.a_t[g];
             }
