@@ -82,6 +82,7 @@ struct gbmc_plan {
     std::vector<int32_t> offset;     // [B+1]
     int32_t n_items[GBMC_N_PASSES] = {0, 0, 0};
     WorkItem* d_items[GBMC_N_PASSES] = {nullptr, nullptr, nullptr};
+    WorkItem* d_near[GBMC_N_PASSES] = {nullptr, nullptr, nullptr};   // in the order of near_first
     void* d_mem = nullptr;           // one allocation: the work lists and the order
     int32_t* d_perm = nullptr;       // [N] internal -> caller atom index
     int32_t* d_offset = nullptr;     // [B+1] device copy of the atom offsets
@@ -141,6 +142,22 @@ static gbmc_status check_offsets(int32_t n_systems, const int32_t* off)
     return GBMC_OK;
 }
 
+// Stable sort of work items by a key of small non-negative integers, by counting
+// (a plan of 32 systems of 4,001 atoms is made in 2.9 ms, with comparisons in 4.2).
+template <class Key>
+static void sort_items(std::vector<WorkItem>& v, Key&& key)
+{
+    std::vector<int32_t> k(v.size());
+    for (size_t n = 0; n < v.size(); ++n) k[n] = key(v[n]);
+    const int32_t top = v.empty() ? 0 : *std::max_element(k.begin(), k.end());
+    std::vector<size_t> at((size_t)top + 2, 0);
+    for (int32_t x : k) ++at[(size_t)x + 1];
+    for (size_t n = 1; n < at.size(); ++n) at[n] += at[n - 1];
+    std::vector<WorkItem> out(v.size());
+    for (size_t n = 0; n < v.size(); ++n) out[at[k[n]]++] = v[n];
+    v.swap(out);
+}
+
 // With row_pairs, the i blocks of a system are taken in pairs (2a, 2a + 1):
 // the tiles of the pair against j blocks J >= 2a + 2 form two-row items; the
 // diagonal band (2a, 2a), (2a, 2a + 1), (2a + 1, 2a + 1) and an unpaired last
@@ -186,8 +203,9 @@ static gbmc_status build_items(int32_t n_systems, const int32_t* off, int32_t jb
     auto cost = [](const WorkItem& w) {
         return 2 * w.rows * (w.J1 - w.J0) - (w.J0 == w.I ? 1 : 0);
     };
-    std::stable_sort(items.begin(), items.end(),
-                     [&](const WorkItem& a, const WorkItem& b) { return cost(a) > cost(b); });
+    int32_t longest = 0;
+    for (const WorkItem& w : items) longest = std::max(longest, cost(w));
+    sort_items(items, [&](const WorkItem& w) { return longest - cost(w); });
     return GBMC_OK;
 }
 
@@ -384,8 +402,7 @@ static void plan_schedule(int32_t n_systems, const int32_t* off, gbmc_precision 
     std::vector<int32_t> pos(n_systems);
     for (int32_t r = 0; r < n_systems; ++r) pos[rank[r]] = r;
     for (int k : {GBMC_PASS_RADII, GBMC_PASS_ENERGY})
-        std::stable_sort(items[k].begin(), items[k].end(),
-                         [&](const WorkItem& a, const WorkItem& c) { return pos[a.sys] < pos[c.sys]; });
+        sort_items(items[k], [&](const WorkItem& w) { return pos[w.sys]; });
     n_blocks = 0;
     for (int32_t b = 0; b < n_systems; ++b) n_blocks += (off[b + 1] - off[b] + kTile - 1) / kTile;
     totals.assign((size_t)GBMC_N_PASSES * n_blocks, 0);
@@ -393,6 +410,24 @@ static void plan_schedule(int32_t n_systems, const int32_t* off, gbmc_precision 
         for (const WorkItem& w : items[k])
             for (int32_t d = 0; d < item_blocks(w); ++d)
                 ++totals[(size_t)k * n_blocks + w.blk0 + item_block(w, d)];
+}
+
+// The list of single tiles of a launch of its own: by distance from the diagonal,
+// nearest first.  In a spatial order of the atoms the near tiles hold the overlapping
+// pairs, which take longest and in the order above end the launch (the
+// diagonal tiles come last of all); and items that run together then add to
+// different rows.  One system of 10,000 atoms: descreening 44.8 -> 41.6 us, energy
+// 54.8 -> 51.7, chain 82.5 -> 76.6; 16 of 2,500: 51.3 -> 49.4, 74.4 -> 73.0, 90.6 -> 86.7;
+// 24 of 65-3,777 with salt, all three: 235 -> 227.  Items that run together also
+// touch every system of the batch, so this holds while its inputs stay in an
+// XCD's 4 MB of L2: 16 of 4,001 (64,016 atoms) 456 -> 446 us, 24 of them 644 -> 645,
+// 32 of them (energies only) 325.5 -> 334.5; long items of 646,341 atoms lose 4 %.
+constexpr int32_t kNearAtoms = 65536;
+
+static std::vector<WorkItem> near_first(std::vector<WorkItem> items)
+{
+    sort_items(items, [](const WorkItem& w) { return w.J0 - w.I - w.rows + 1; });
+    return items;
 }
 
 gbmc_status gbmc_schedule_build(int32_t n_systems, const int32_t* host_atom_offset,
@@ -535,14 +570,19 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
         p->scratch_err = scratch_address(p->device, &p->scratch);
         e = hipDeviceGetAttribute(&p->n_cu, hipDeviceAttributeMultiprocessorCount, p->device);
         if (e != hipSuccess) { delete p; return hip_fail(e, "hipDeviceGetAttribute"); }
-        // one device allocation: the three work lists, then the processing order (identity)
-        size_t at[GBMC_N_PASSES + 1];
+        // one device allocation: the three work lists (single tiles twice: the queued
+        // launch has its own order), then the processing order (identity)
+        size_t at[GBMC_N_PASSES + 1], at_near[GBMC_N_PASSES];
+        std::vector<WorkItem> near[GBMC_N_PASSES];
         size_t o = 0;
         for (int k = 0; k < GBMC_N_PASSES; ++k) {
             if (items[k].size() > 0x7fffffff) { delete p; return fail(GBMC_ERR_UNSUPPORTED, "too many work items"); }
             p->n_items[k] = (int32_t)items[k].size();
             at[k] = o;
             o = align256(o + items[k].size() * sizeof(WorkItem));
+            if (t.j_blocks_per_item[k] == 1 && p->n_atoms <= kNearAtoms) near[k] = near_first(items[k]);
+            at_near[k] = o;
+            o = align256(o + near[k].size() * sizeof(WorkItem));
         }
         at[GBMC_N_PASSES] = o;
         const size_t off_bytes = 4 * (size_t)(n_systems + 1);
@@ -562,6 +602,9 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
                 p->d_items[k] = reinterpret_cast<WorkItem*>(d + at[k]);
                 if (!items[k].empty())
                     std::memcpy(h.data() + at[k], items[k].data(), items[k].size() * sizeof(WorkItem));
+                p->d_near[k] = near[k].empty() ? p->d_items[k] : reinterpret_cast<WorkItem*>(d + at_near[k]);
+                if (!near[k].empty())
+                    std::memcpy(h.data() + at_near[k], near[k].data(), near[k].size() * sizeof(WorkItem));
             }
             p->d_perm = reinterpret_cast<int32_t*>(d + at[GBMC_N_PASSES]);
             int32_t* id = reinterpret_cast<int32_t*>(h.data() + at[GBMC_N_PASSES]);
@@ -801,7 +844,7 @@ static bool uses_cutoffs(const GBConst& c) { return c.rgbmax > 0.0 || c.cutoff >
 
 static PassShape pass_shape(const gbmc_plan* p, int k)
 {
-    return PassShape{p->d_items[k], p->n_items[k], p->tuning.waves_per_group[k],
+    return PassShape{p->d_near[k], p->n_items[k], p->tuning.waves_per_group[k],
                      p->tuning.j_blocks_per_item[k] == 1, p->wide[k],
                      p->d_total + (size_t)k * p->n_blocks};
 }
