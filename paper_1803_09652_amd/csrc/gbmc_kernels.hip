@@ -2715,19 +2715,36 @@ __global__ __launch_bounds__(kSDE) void k_site_dE(
     const int ns = sd.site_state_offset[m + 1] - g0;
     const int cur = current_state[m];
     const int nc = ns - 1;
-    const int sa_site0 = sd.site_sa_offset[m];
+    const int sa_site0 = sd.site_sa_offset[m], cand0 = sd.cand_offset[m];
     const double* qcur = sd.state_charges + sd.state_charge_offset[g0 + cur];
+    // The kernel is a chain of dependent loads (12.4 us with the candidates' charges
+    // loaded one after the other and the drive of Delta G at the end, now 11.8).  The
+    // charges of all candidates come at once (past the last: its copy), and
+    // the thread of candidate c = t has its drive and reference on the way.
+    const double* qnew[kMaxStates - 1];
+#pragma unroll
+    for (int c = 0; c < kMaxStates - 1; ++c)
+        qnew[c] = sd.state_charges + sd.state_charge_offset[g0 + min(c < cur ? c : c + 1, ns - 1)];
+    double drive = 0.0, gref = 0.0;
+    if (dG && t < nc) {
+        const int b = sd.site_system[m], s_new = t < cur ? t : t + 1;
+        const double per = sd.site_kind[m] == 0 ? kKB * T_kelvin * kLn10 * pH[b] : kFaraday * E_volt[b];
+        drive = per * (double)(sd.state_count[g0 + s_new] - sd.state_count[g0 + cur]);
+        gref = sd.state_gref[g0 + s_new] - sd.state_gref[g0 + cur];
+    }
     for (int a = t; a < na; a += kSDE) {
         int g = sd.site_atoms[a0 + a];
+        double dq[kMaxStates - 1];
+        const double q0 = qcur[a];
+#pragma unroll
+        for (int c = 0; c < kMaxStates - 1; ++c) dq[c] = qnew[c][a] - q0;
         const double R = rows[g].R;
         sx[a] = X[g]; sy[a] = Y[g]; sz[a] = Z[g]; sR[a] = R; sA[a] = rows[g].A;
         double phi = -gb_kd(R, kC, kT, kO, kap) * (double)Q[g] / R;   // self term
         phi += (double)(long long)phi_fx[sa_site0 + a] * (1.0 / kScaleP);
         sphi[a] = phi;
-        for (int c = 0; c < nc; ++c) {
-            int s_new = c < cur ? c : c + 1;
-            sdq[c][a] = sd.state_charges[sd.state_charge_offset[g0 + s_new] + a] - qcur[a];
-        }
+#pragma unroll
+        for (int c = 0; c < kMaxStates - 1; ++c) sdq[c][a] = dq[c];
     }
     __syncthreads();
     double part[2 * (kMaxStates - 1)];
@@ -2761,17 +2778,10 @@ __global__ __launch_bounds__(kSDE) void k_site_dE(
     for (int c = 0; c < kMaxStates - 1; ++c)
         if (c == t) { lin = part[c]; quad = part[kMaxStates - 1 + c]; }
     if (t < nc) {
-        int c = t;
-        int s_new = c < cur ? c : c + 1;
-        double de = lin + 0.5 * quad;
-        int cand = sd.cand_offset[m] + c;
+        const double de = lin + 0.5 * quad;
+        const int cand = cand0 + t;
         dE[cand] = de;
-        if (dG) {
-            int b = sd.site_system[m];
-            double drive = sd.site_kind[m] == 0 ? kKB * T_kelvin * kLn10 * pH[b] : kFaraday * E_volt[b];
-            dG[cand] = de + drive * (double)(sd.state_count[g0 + s_new] - sd.state_count[g0 + cur])
-                     - (sd.state_gref[g0 + s_new] - sd.state_gref[g0 + cur]);
-        }
+        if (dG) dG[cand] = de + drive - gref;
     }
 }
 
@@ -2792,94 +2802,111 @@ __global__ __launch_bounds__(kMC) void k_mc_step(
     int32_t* __restrict__ n_electrons, int64_t* __restrict__ counters,
     int32_t* __restrict__ accepted)
 {
-    __shared__ double red[1][4];
+    __shared__ double red[1][kMC / kTile];
+    __shared__ double sx[2][kMaxSiteAtoms], sy[2][kMaxSiteAtoms], sz[2][kMaxSiteAtoms];
+    __shared__ double sR[2][kMaxSiteAtoms], sA[2][kMaxSiteAtoms], sdq[2][kMaxSiteAtoms];
     const int b = blockIdx.x;
     const int t = threadIdx.x;
     const double* ub = u + 6 * (size_t)b;
     const double kTB = kKB * T_kelvin;
-    int acc_p = 0, m_p = -1, s_p = 0, snew_p = 0;
-    // ---- protonation attempt
-    {
-        const int p0 = sd.sys_prot_offset[b], np = sd.sys_prot_offset[b + 1] - p0;
-        if (np > 0) {
-            m_p = sd.sys_prot_sites[p0 + pick_index(ub[0], np)];
-            const int g0 = sd.site_state_offset[m_p];
-            const int ns = sd.site_state_offset[m_p + 1] - g0;
-            s_p = current_state[m_p];
-            const int tp = pick_index(ub[1], ns - 1);
-            snew_p = tp < s_p ? tp : tp + 1;
-            const double dg = dGin[sd.cand_offset[m_p] + tp];
-            acc_p = ub[2] < exp(-dg / kTB) ? 1 : 0;
-        }
-    }
-    // ---- redox attempt, on the charges left by the protonation attempt
-    int acc_r = 0, m_r = -1, s_r = 0, snew_r = 0;
-    {
-        const int r0 = sd.sys_redox_offset[b], nr = sd.sys_redox_offset[b + 1] - r0;
-        if (nr > 0) {
-            m_r = sd.sys_redox_sites[r0 + pick_index(ub[3], nr)];
-            const int g0 = sd.site_state_offset[m_r];
-            const int ns = sd.site_state_offset[m_r + 1] - g0;
-            s_r = current_state[m_r];
-            const int tp = pick_index(ub[4], ns - 1);
-            snew_r = tp < s_r ? tp : tp + 1;
-            double dg = dGin[sd.cand_offset[m_r] + tp];
-            if (acc_p) {
-                // cross term dq_redox . K . dq_prot (sites are disjoint)
-                const int ar0 = sd.site_atom_offset[m_r], nar = sd.site_atom_offset[m_r + 1] - ar0;
-                const int ap0 = sd.site_atom_offset[m_p], nap = sd.site_atom_offset[m_p + 1] - ap0;
-                const int gp0 = sd.site_state_offset[m_p];
-                const double* qr1 = sd.state_charges + sd.state_charge_offset[g0 + snew_r];
-                const double* qr0 = sd.state_charges + sd.state_charge_offset[g0 + s_r];
-                const double* qp1 = sd.state_charges + sd.state_charge_offset[gp0 + snew_p];
-                const double* qp0 = sd.state_charges + sd.state_charge_offset[gp0 + s_p];
-                double part[1] = {0.0};
-                for (int p = t; p < nar * nap; p += kMC) {
-                    int a = p / nap, c = p - a * nap;
-                    int ga = sd.site_atoms[ar0 + a], gc = sd.site_atoms[ap0 + c];
-                    double K = pairK((double)X[ga] - (double)X[gc], (double)Y[ga] - (double)Y[gc],
-                                     (double)Z[ga] - (double)Z[gc], rows[ga].R, rows[ga].A,
-                                     rows[gc].R, rows[gc].A, kC, kT, kO, kap, cut2);
-                    part[0] += (qr1[a] - qr0[a]) * (qp1[c] - qp0[c]) * K;
-                }
-                block_sum<1, kMC / kTile>(red, part);
-                dg += part[0];
-            }
-            acc_r = ub[5] < exp(-dg / kTB) ? 1 : 0;
-        }
-    }
-    // ---- apply
-    __syncthreads();
-    for (int pass = 0; pass < 2; ++pass) {
-        const int m = pass == 0 ? m_p : m_r;
-        const int acc = pass == 0 ? acc_p : acc_r;
-        const int snew = pass == 0 ? snew_p : snew_r;
-        if (m < 0) continue;
-        if (acc) {
-            const int a0 = sd.site_atom_offset[m], na = sd.site_atom_offset[m + 1] - a0;
-            const double* qn = sd.state_charges + sd.state_charge_offset[sd.site_state_offset[m] + snew];
-            for (int a = t; a < na; a += kMC) Q[sd.site_atoms[a0 + a]] = (T)qn[a];
-        }
+    if (sd.n_sites == 0) {
         if (t == 0) {
-            if (acc) current_state[m] = snew;
+            if (accepted) accepted[2 * b] = accepted[2 * b + 1] = 0;
+            if (n_electrons) n_electrons[b] = 0;
+        }
+        return;
+    }
+    // Both attempts' tables (0 protonation, 1 redox) come together, level by level, since
+    // the kernel is a chain of dependent loads; and the atoms of both sites are staged
+    // once, whether the cross term will be needed or not (gathered anew for each
+    // pair of atoms they cost 3.4 us: 12.5 -> 9.1 on 16 systems of 8 sites).  A system without a site of one kind follows site 0 and drops the result.
+    const int32_t* const offs[2] = {sd.sys_prot_offset, sd.sys_redox_offset};
+    const int32_t* const list[2] = {sd.sys_prot_sites, sd.sys_redox_sites};
+    int o0[2], n[2], m[2], g0[2], s_old[2], s_new[2], cand[2], a0[2], na[2];
+    double dg[2];
+    const double *qn[2], *qo[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) { o0[k] = offs[k][b]; n[k] = offs[k][b + 1] - o0[k]; }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int32_t* at = n[k] > 0 ? list[k] + o0[k] + pick_index(ub[3 * k], n[k]) : sd.site_atom_offset;
+        m[k] = *at;
+        if (n[k] == 0) m[k] = 0;
+    }
+    int ns[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        g0[k] = sd.site_state_offset[m[k]];
+        ns[k] = sd.site_state_offset[m[k] + 1] - g0[k];
+        s_old[k] = current_state[m[k]];
+        cand[k] = sd.cand_offset[m[k]];
+        a0[k] = sd.site_atom_offset[m[k]];
+        na[k] = sd.site_atom_offset[m[k] + 1] - a0[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int tp = pick_index(ub[3 * k + 1], ns[k] - 1);
+        s_new[k] = tp < s_old[k] ? tp : tp + 1;
+        dg[k] = dGin[cand[k] + tp];
+        qn[k] = sd.state_charges + sd.state_charge_offset[g0[k] + s_new[k]];
+        qo[k] = sd.state_charges + sd.state_charge_offset[g0[k] + s_old[k]];
+    }
+    for (int w = t; w < 2 * kMaxSiteAtoms; w += kMC) {
+        const int k = w / kMaxSiteAtoms, a = w % kMaxSiteAtoms;
+        if (a >= na[k]) continue;
+        const int g = sd.site_atoms[a0[k] + a];
+        sx[k][a] = (double)X[g]; sy[k][a] = (double)Y[g]; sz[k][a] = (double)Z[g];
+        sR[k][a] = rows[g].R; sA[k][a] = rows[g].A;
+        sdq[k][a] = qn[k][a] - qo[k][a];
+    }
+    __syncthreads();
+    int acc[2];
+    acc[0] = n[0] > 0 && ub[2] < exp(-dg[0] / kTB) ? 1 : 0;
+    // the redox attempt, on the charges left by the protonation attempt
+    if (acc[0] && n[1] > 0) {
+        // cross term dq_redox . K . dq_prot (sites are disjoint)
+        double part[1] = {0.0};
+        for (int p = t; p < na[1] * na[0]; p += kMC) {
+            const int a = p / na[0], c = p - a * na[0];
+            const double K = pairK(sx[1][a] - sx[0][c], sy[1][a] - sy[0][c], sz[1][a] - sz[0][c],
+                                   sR[1][a], sA[1][a], sR[0][c], sA[0][c], kC, kT, kO, kap, cut2);
+            part[0] += sdq[1][a] * sdq[0][c] * K;
+        }
+        block_sum<1, kMC / kTile>(red, part);
+        dg[1] += part[0];
+    }
+    acc[1] = n[1] > 0 && ub[5] < exp(-dg[1] / kTB) ? 1 : 0;
+    // apply: each half of the workgroup one attempt, the last wavefront the electron
+    // count, one redox site per lane
+    __syncthreads();
+    const int h = t / (kMC / 2), th = t % (kMC / 2);
+    if (n_electrons && t >= kMC - kTile) {
+        int ne = 0;
+        for (int k = t - (kMC - kTile); k < n[1]; k += kTile) {
+            const int mk = sd.sys_redox_sites[o0[1] + k];
+            const int st = mk != m[1] ? current_state[mk] : acc[1] ? s_new[1] : s_old[1];
+            ne += sd.state_count[sd.site_state_offset[mk] + st];
+        }
+#pragma unroll
+        for (int off = kTile / 2; off > 0; off >>= 1) ne += __shfl_xor(ne, off);
+        if (t == kMC - kTile) n_electrons[b] = ne;
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        if (h != k || n[k] == 0) continue;
+        if (acc[k])
+            for (int a = th; a < na[k]; a += kMC / 2) Q[sd.site_atoms[a0[k] + a]] = (T)qn[k][a];
+        if (th == 0) {
+            if (acc[k]) current_state[m[k]] = s_new[k];
             if (counters) {
-                counters[2 * (size_t)m] += 1;
-                counters[2 * (size_t)m + 1] += acc;
+                counters[2 * (size_t)m[k]] += 1;
+                counters[2 * (size_t)m[k] + 1] += acc[k];
             }
         }
     }
-    if (t == 0) {
-        if (accepted) { accepted[2 * b] = acc_p; accepted[2 * b + 1] = acc_r; }
-        if (n_electrons) {
-            const int r0 = sd.sys_redox_offset[b], nr = sd.sys_redox_offset[b + 1] - r0;
-            int ne = 0;
-            for (int k = 0; k < nr; ++k) {
-                int m = sd.sys_redox_sites[r0 + k];
-                int st = (m == m_r && acc_r) ? snew_r : current_state[m];
-                ne += sd.state_count[sd.site_state_offset[m] + st];
-            }
-            n_electrons[b] = ne;
-        }
+    if (t == 0 && accepted) {
+        accepted[2 * b] = acc[0];
+        accepted[2 * b + 1] = acc[1];
     }
 }
 
@@ -2893,7 +2920,7 @@ __global__ __launch_bounds__(kMC) void k_mc_step(
 // formed each visit's terms in turn, and added K dq to every site atom's
 // potential after each acceptance, was a chain of dependent loads, block
 // reductions and rows of FP64 pair terms on one CU: 158 us on 16 systems of 356
-// site atoms, against 26 us for the two kernels.)
+// site atoms, against 23 us for the two kernels.)
 
 // The state a sweep proposes for site m.
 __device__ __forceinline__ int sweep_proposal(const SiteDev& sd, int m, int s, const double* u)
@@ -2922,6 +2949,8 @@ __global__ __launch_bounds__(kCouple) void k_site_couple(
     const bool same = m[0] == m[1];
     if (!(kinds & (1 << sd.site_kind[m[0]])) || !(kinds & (1 << sd.site_kind[m[1]]))) return;
     double part[1] = {0.0};
+    const int sys = sd.site_system[m[0]], s0 = sd.sys_site_offset[sys], S = sd.sys_site_offset[sys + 1] - s0;
+    double* const c_out = couple + sd.sys_couple_offset[sys];
     // half of the workgroup stages each site
     const int h = t / (kCouple / 2), a = t % (kCouple / 2);
     static_assert(kCouple / 2 >= kMaxSiteAtoms, "one staging thread per site atom");
@@ -2970,11 +2999,9 @@ __global__ __launch_bounds__(kCouple) void k_site_couple(
     }
     block_sum<1, kCouple / kTile>(red, part);
     if (t == 0) {
-        const int b = sd.site_system[m[0]], s0 = sd.sys_site_offset[b], S = sd.sys_site_offset[b + 1] - s0;
-        double* c = couple + sd.sys_couple_offset[b];
         const int i = m[0] - s0, j = m[1] - s0;
-        c[(size_t)i * S + j] = part[0];
-        c[(size_t)j * S + i] = part[0];
+        c_out[(size_t)i * S + j] = part[0];
+        c_out[(size_t)j * S + i] = part[0];
     }
 }
 
@@ -2994,6 +3021,7 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
     // acceptance uniform; visiting order, current and proposed state, decision
     __shared__ double dg[kMaxSweepSites], dg_at[kMaxSweepSites], su[kMaxSweepSites];
     __shared__ int order[kMaxSweepSites];
+    __shared__ unsigned short site_of[kMaxSweepSites];
     __shared__ unsigned char st[kMaxSweepSites], st_new[kMaxSweepSites], acc[kMaxSweepSites];
     const int b = blockIdx.x, t = threadIdx.x;
     const int s0 = sd.sys_site_offset[b], S = sd.sys_site_offset[b + 1] - s0;
@@ -3021,20 +3049,24 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
         __syncthreads();
         // rank of each site by (u[3m], m); a NaN key sorts last, so the ranks
         // always form a permutation
-        auto order_key = [&](int m) {
-            const double k = u[3 * (size_t)m];
-            return k == k ? k : 2.0;
-        };
+        // (a site's key waits in dg_at, which its visit overwrites)
         for (int k = t; k < cnt; k += kSweep) {
             const int m = list[k];
-            const double key = order_key(m);
+            const double key = u[3 * (size_t)m];
+            dg_at[m - s0] = key == key ? key : 2.0;
+            site_of[k] = m - s0;
+        }
+        __syncthreads();
+        for (int k = t; k < cnt; k += kSweep) {
+            const int i = site_of[k];
+            const double key = dg_at[i];
             int rank = 0;
             for (int j = 0; j < cnt; ++j) {
-                const int mj = list[j];
-                const double kj = order_key(mj);
-                rank += (kj < key) || (kj == key && mj < m);
+                const int ij = site_of[j];
+                const double kj = dg_at[ij];
+                rank += (kj < key) || (kj == key && ij < i);
             }
-            order[rank] = m - s0;
+            order[rank] = i;
         }
         __syncthreads();
         for (int v = 0; v < cnt; ++v) {
@@ -3066,20 +3098,24 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
         }
         if (acc[i]) current_state[m] = st_new[i];
     }
-    for (int i = 0; i < S; ++i) {
+    // one wavefront per accepted site, and the electron count one redox site per thread
+    const int wave = t / kTile, lane = t % kTile;
+    for (int i = wave; i < S; i += kSweep / kTile) {
         if (!acc[i]) continue;
         const int m = s0 + i, a0 = sd.site_atom_offset[m], na = sd.site_atom_offset[m + 1] - a0;
         const double* qn = sd.state_charges + sd.state_charge_offset[sd.site_state_offset[m] + st_new[i]];
-        for (int a = t; a < na; a += kSweep) Qout[sd.site_atoms[a0 + a]] = (T)qn[a];
+        for (int a = lane; a < na; a += kTile) Qout[sd.site_atoms[a0 + a]] = (T)qn[a];
     }
-    if (t == 0 && n_electrons) {
+    if (wave == 0 && n_electrons) {
         const int r0 = sd.sys_redox_offset[b], nr = sd.sys_redox_offset[b + 1] - r0;
         int ne = 0;
-        for (int k = 0; k < nr; ++k) {
+        for (int k = lane; k < nr; k += kTile) {
             const int m = sd.sys_redox_sites[r0 + k], i = m - s0;
             ne += sd.state_count[sd.site_state_offset[m] + (acc[i] ? st_new[i] : st[i])];
         }
-        n_electrons[b] = ne;
+#pragma unroll
+        for (int off = kTile / 2; off > 0; off >>= 1) ne += __shfl_xor(ne, off);
+        if (lane == 0) n_electrons[b] = ne;
     }
 }
 
