@@ -573,9 +573,7 @@ class GBEnergy(torch.autograd.Function):
         pos_d, q_d, rho_d, scr_d = (t.detach() for t in (pos, q, rho, screen))
         atoms = Atoms(plan, pos_d[:, 0], pos_d[:, 1], pos_d[:, 2], q_d, rho_d, scr_d)
         ws = torch.empty_like(plan.workspace)
-        radii(plan, atoms, params, workspace=ws)
-        out = energy_forces(plan, atoms, params, force=False, dEdq=False, dEdrho=False,
-                            workspace=ws)
+        out = evaluate(plan, atoms, params, force=False, dEdq=False, dEdrho=False, workspace=ws)
         ctx.plan, ctx.params, ctx.atoms, ctx.ws = plan, params, atoms, ws
         return out["e_coul"] + out["e_gb"]
 
