@@ -135,7 +135,8 @@ class ReplicaMD:
         noise = torch.empty((3, N), dtype=plan.dtype, device=dev)
         # the call's buffers and argument lists, built once: a step is then a few
         # library calls, 20 us of host time for 47 with the per-call wrappers (16 x 237
-        # atoms, where the host bounds the loop)
+        # atoms, where the host bounds the loop).  The lists hold raw addresses: `out`
+        # keeps every output tensor until the last call is queued.
         out = api._eval_outputs(plan, True, False, False)
         f = out["force"]
         noises = [noise] * n_steps if xi is None else xi.unbind(0)
@@ -162,9 +163,9 @@ class ReplicaMD:
                     torch.rand((B, 6), dtype=torch.float64, device=dev, generator=self.gen)
                 dE, dG = api.mc_state_dE(plan, self.sites, self.atoms, self.state, self.pH,
                                          self.E_rep, self.T, self.params)
-                out = api.mc_step(plan, self.sites, self.atoms, self.state, self.pH, self.E_rep,
-                                  dE, dG, u, self.T, self.params, counters=self.counters)
-                self.n_electrons.copy_(out["n_electrons"])
+                mc = api.mc_step(plan, self.sites, self.atoms, self.state, self.pH, self.E_rep,
+                                 dE, dG, u, self.T, self.params, counters=self.counters)
+                self.n_electrons.copy_(mc["n_electrons"])
                 if record:
                     rec["state"][a_i].copy_(self.state[:S])
                     rec["rep_of_rung"][a_i].copy_(self.rep_of_rung)
