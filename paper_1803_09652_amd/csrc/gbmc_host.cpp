@@ -974,8 +974,14 @@ static gbmc_status evaluate_impl(gbmc_plan* p, const gbmc_atoms* a, const gbmc_g
         if (e == hipSuccess) e = hipStreamWaitEvent(fork, p->fork_ev, 0);
         return e == hipSuccess ? GBMC_OK : hip_fail(e, "gb_evaluate_fork: fork event");
     };
-    if (p->n_atoms == 0) return mark();
     GBConst c = make_const(gp);
+    if (p->n_atoms == 0) {
+        // the energies of empty systems (no array is read, and `a` may be NULL)
+        const gbmc_atoms none{};
+        hipError_t e = energy_launch(p, &none, c, ws, e_coul, e_gb, force, dEdq, dEdrho, s, false,
+                                     false, nullptr);
+        return e == hipSuccess ? mark() : hip_fail(e, "gb_evaluate launch");
+    }
     // in single-launch mode the three all-pairs passes of a full evaluation
     // (forces or dE/drho requested, no cutoffs) run as one queued launch
     const bool chain = force || dEdrho;

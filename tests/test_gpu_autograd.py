@@ -9,6 +9,8 @@ differentiable function of positions, charges and intrinsic radii.
   central differences of the FP64 GPU energies, and torch.autograd.gradcheck
   on a tiny system.
 """
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -170,3 +172,32 @@ def test_fp64_gradients_with_salt_and_cutoffs():
         assert rel_inf(pos.grad[s0:s1].cpu().numpy(), -wb * ref["F"]) <= t["grad"]
         assert rel_inf(q.grad[s0:s1].cpu().numpy(), wb * ref["phi"]) <= t["grad"]
         assert rel_inf(rho.grad[s0:s1].cpu().numpy(), wb * ref["dEdrho"]) <= t["grad"]
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("single_launch", [False, True])
+def test_batch_without_atoms_has_zero_energies(prec, single_launch, monkeypatch):
+    # every system empty: both energies are written (outputs start as NaN)
+    g = gb()
+    empty = torch.empty
+
+    def nan_filled(*a, **k):
+        t = empty(*a, **k)
+        return t.fill_(float("nan")) if t.is_floating_point() else t
+    monkeypatch.setattr(torch, "empty", nan_filled)
+    plan = g.Plan([0, 0, 0, 0], prec)
+    plan.set_single_launch(single_launch)
+    v = torch.zeros(0, dtype=plan.dtype, device=plan.device)
+    atoms = g.Atoms(plan, v, v, v, v, v, v)
+    cut = dataclasses.replace(params_pair()[0], rgbmax=10.0, cutoff=12.0)
+    for kw in ({}, dict(force=False, dEdq=False, dEdrho=False), dict(fork=torch.cuda.Stream()),
+               dict(params=cut)):
+        out = g.evaluate(plan, atoms, **{"params": params_pair()[0], **kw})
+        torch.cuda.synchronize()
+        assert out["e_coul"].tolist() == [0.0] * 3 and out["e_gb"].tolist() == [0.0] * 3
+    pos = torch.zeros((0, 3), dtype=plan.dtype, device=plan.device, requires_grad=True)
+    q, rho = v.clone().requires_grad_(True), v.clone().requires_grad_(True)
+    E = g.GBEnergy.apply(pos, q, rho, v, plan, params_pair()[0])
+    E.sum().backward()
+    assert E.tolist() == [0.0] * 3
+    assert pos.grad.shape == (0, 3) and q.grad.shape == (0,) and rho.grad.shape == (0,)
