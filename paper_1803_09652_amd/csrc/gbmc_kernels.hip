@@ -86,8 +86,9 @@ __device__ __forceinline__ double exp2neg(double t)
 
 // 1/a and 1/b from one reciprocal: c = 1/(a b), 1/a = c b, 1/b = c a (a
 // transcendental costs several ordinary instructions).  For the polynomial
-// forms of the chain pass, where a, b = 1 - y >= 0.6 for every pair whose terms
-// are kept.
+// forms of the chain pass, where a, b = 1 - y >= 0.6 wherever both results are
+// kept.  A zero or an infinite a takes 1/b with it: a caller that keeps one
+// result and replaces the other bounds its arguments first.
 __device__ __forceinline__ void rcp_pair(float a, float b, float& ia, float& ib)
 {
     const float c = rcp(a * b);
@@ -845,7 +846,11 @@ __device__ __forceinline__ void chain_pair_cutf(T r, T r2, T invr, T rti, T Si, 
         wij = hct_w_far(yij);
         wji = hct_w_far(yji);
     } else {
-        rcp_pair(T(1) - yij, T(1) - yji, wij, wji);
+        // (a direction beyond the polynomial form is replaced below, the other one kept:
+        // its 1 - y may be zero, where S_j = r, and is bounded from below.  Directions
+        // within the form lie above the bound.)
+        const T low = T(1) - y_max<T>();
+        rcp_pair(max(T(1) - yij, low), max(T(1) - yji, low), wij, wji);
         wij *= wij;
         wji *= wji;
     }
