@@ -2609,7 +2609,7 @@ __device__ __forceinline__ double pairK_row(double dx, double dy, double dz, dou
     const double invf = rsq64(f2);
     const double kd = SALT ? kC - kO * exp2neg(kap * kLog2e * (f2 * invf)) : kT;
     const double K = kC * invr - kd * invf;
-    return r2 < cut2 ? K : 0.0;
+    return r2 >= cut2 ? 0.0 : K;        // (a NaN passes, and raises the flag)
 }
 
 // One lane per site atom.  The chunk's j atoms (positions and radii of the

@@ -3,6 +3,8 @@ with sites of 1, 64, 255 and 256 atoms (the most a site may have), against the
 oracle: FP64 plan, several attempts from the states the ones before left.  Delta G
 at 1e-9 relative, decisions, states, charges, counters and electron counts equal
 (no uniform lies within 1e-9 of its acceptance probability)."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -91,3 +93,21 @@ def test_attempts_on_missing_kinds_and_large_sites(T):
     total = counters.cpu().numpy().sum(0)
     tried = 6 * sum((any(k == 0 for k, _ in v)) + (any(k == 1 for k, _ in v)) for v in SITES)
     assert total[0] == tried and total[1] == n_acc
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("kappa", [0.0, 0.1])
+def test_undefined_distance_raises_the_flag(prec, kappa):
+    # a coordinate that is not a number: the potential rows raise the flag by themselves,
+    # after the one that the radii raised has been read (which clears it)
+    s = synth.make_system(216, 300, 9.0, n_redox=1, n_prot=1)
+    far = [a for a in range(s.n) if all(a not in site.atoms for site in s.sites)]
+    s.y[far[0]] = np.nan
+    p = dataclasses.replace(params_pair()[0], kappa=kappa)
+    g, batch, plan, atoms = build([s], prec)
+    sites = g.Sites.from_batch(plan, batch)
+    cur = torch.as_tensor(batch.current_state, device=plan.device)
+    g.radii(plan, atoms, p)
+    assert g.check_overflow(plan) and not g.check_overflow(plan)
+    g.mc_state_dE(plan, sites, atoms, cur, 7.0, -0.2, 300.0, p)
+    assert g.check_overflow(plan)
