@@ -320,8 +320,8 @@ int32_t gbmc_sites_n_candidates(const gbmc_sites* sites);
 /* Bytes of caller-owned device workspace mc_state_dE, mc_step and mc_sweep need:
  * the site atoms' FP64 potentials as int64 fixed point (2^-44 kcal/mol/e), which
  * mc_state_dE and mc_sweep clear and fill on every call, and (where mc_sweep
- * supports the sites) a double for every two sites of a system, which mc_sweep
- * fills with their couplings. */
+ * supports the sites) a double for every two sites of a system, or in batches
+ * of very many sites for every site, which mc_sweep fills with their couplings. */
 size_t gbmc_sites_workspace_bytes(const gbmc_sites* sites);
 
 /* Delta E_elec and Delta G of every candidate state change (sections II.A-B):

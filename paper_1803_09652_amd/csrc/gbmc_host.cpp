@@ -1162,22 +1162,27 @@ gbmc_status gbmc_sites_create(gbmc_plan* p, gbmc_sites** out, int32_t n_sites,
         std::vector<int32_t> sys_site(B + 1, 0), couples;
         std::vector<int64_t> couple_off(B + 1, 0);
         bool sweep_ok = true;
+        int64_t n_pairs = 0, most = 0;
         for (int32_t b = 0; b < B; ++b) {
             const int32_t s0 = first[b] >= 0 ? first[b] : sys_site[b];
             sys_site[b] = s0;
             sys_site[b + 1] = first[b] >= 0 ? last[b] + 1 : s0;
+            const int64_t n = sys_site[b + 1] - s0;
+            n_pairs += n * (n + 1) / 2;
+            most = std::max(most, n);
             sweep_ok = sweep_ok && sys_sa[b + 1] - sys_sa[b] <= kMaxSweepSiteAtoms;
         }
+        const bool sweep_live = n_pairs > kSweepPairs * most;
         for (int32_t b = 0; sweep_ok && b < B; ++b) {
             const int32_t n = sys_site[b + 1] - sys_site[b];
-            couple_off[b + 1] = couple_off[b] + (int64_t)n * n;
+            couple_off[b + 1] = couple_off[b] + (sweep_live ? n : (int64_t)n * n);
+            if (sweep_live) continue;
             for (int32_t i = sys_site[b]; i < sys_site[b + 1]; ++i)
                 for (int32_t j = i; j < sys_site[b + 1]; ++j) {
                     couples.push_back(i);
                     couples.push_back(j);
                 }
         }
-        if (couples.size() / 2 > 0x7fffffff) return fail(GBMC_ERR_UNSUPPORTED, "too many pairs of sites");
         // one device allocation for every table
         size_t o = 0;
         auto seg = [&](size_t bytes) { size_t at = o; o = align256(o + bytes); return at; };
@@ -1251,8 +1256,9 @@ gbmc_status gbmc_sites_create(gbmc_plan* p, gbmc_sites** out, int32_t n_sites,
         sd.site_sa_offset = sd.site_atom_offset;
         sd.sys_sa_offset = (const int32_t*)(d + o_syssa);
         sd.rowitems = (const RowItem*)(d + o_rows);
-        sd.n_couples = (int32_t)(couples.size() / 2);
-        sd.couples = (const int32_t*)(d + o_cp);
+        sd.sweep_live = sweep_live;
+        sd.n_couples = sweep_live ? S : (int32_t)(couples.size() / 2);
+        sd.couples = sweep_live ? nullptr : (const int32_t*)(d + o_cp);
         sd.sys_site_offset = (const int32_t*)(d + o_ss);
         sd.sys_couple_offset = (const int64_t*)(d + o_co);
         *out = sp;
@@ -1361,13 +1367,13 @@ gbmc_status mc_sweep(gbmc_plan* p, const gbmc_sites* s, const gbmc_atoms* a, voi
     GBConst c = make_const(gp);
     hipError_t e;
     if (p->prec == GBMC_FP32_FIXED)
-        e = launch_mc_sweep<float>(s->dev, p->n_sys, s->max_all_sites, (const float*)a->x,
+        e = launch_mc_sweep<float>(s->dev, p->n_sys, s->max_all_sites, s->max_sys_site_atoms, (const float*)a->x,
                                    (const float*)a->y, (const float*)a->z, (const float*)a->q,
                                    (float*)q, c, carve<float>(p, ws), (unsigned long long*)sws,
                                    (double*)sws + s->n_site_atoms, current_state, pH, E_volt, T, kinds, u, n_electrons, counters,
                                    accepted, dG, stream);
     else
-        e = launch_mc_sweep<double>(s->dev, p->n_sys, s->max_all_sites, (const double*)a->x,
+        e = launch_mc_sweep<double>(s->dev, p->n_sys, s->max_all_sites, s->max_sys_site_atoms, (const double*)a->x,
                                     (const double*)a->y, (const double*)a->z, (const double*)a->q,
                                     (double*)q, c, carve<double>(p, ws), (unsigned long long*)sws,
                                     (double*)sws + s->n_site_atoms, current_state, pH, E_volt, T, kinds, u, n_electrons, counters,

@@ -11,6 +11,9 @@ constexpr int kMaxSiteAtoms = 256;
 constexpr int kMaxStates = 8;
 constexpr int kMaxSweepSites = 1024;      // sites of one kind per system in mc_sweep
 constexpr int kMaxSweepSiteAtoms = 1024;  // site atoms per system in mc_sweep (LDS)
+// Pairs of sites of the whole batch, for each site of its largest system, up to which
+// mc_sweep forms the couplings of all pairs before the first decision (see k_mc_sweep).
+constexpr int64_t kSweepPairs = 512;
 #ifndef GBMC_PHI_CHUNK
 #define GBMC_PHI_CHUNK 32
 #endif
@@ -162,7 +165,9 @@ struct SiteDev {
     const int32_t* sys_sa_offset;     // [B+1]
     const RowItem* rowitems;
     // the sequential sweep: the pairs of sites (m <= m') of every system, and where
-    // a system's S x S couplings start
+    // a system's S x S couplings start; with more pairs than kSweepPairs allows
+    // (sweep_live) each site with itself only (couples NULL), one number per site
+    bool sweep_live;
     int32_t n_couples;
     const int32_t* couples;           // [2 n_couples]
     const int32_t* sys_site_offset;   // [B+1]
@@ -266,7 +271,7 @@ hipError_t launch_mc_step(const SiteDev& sd, int n_sys, const T* x, const T* y, 
                           int32_t* n_electrons, int64_t* counters, int32_t* accepted,
                           hipStream_t s, hipEvent_t* ev);
 template <typename T>
-hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, const T* x, const T* y,
+hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, int max_site_atoms, const T* x, const T* y,
                            const T* z, const T* q, T* q_out, const GBConst& c, const Work<T>& w,
                            unsigned long long* phi_fx, double* couple, int32_t* current_state,
                            const double* pH, const double* E_volt, double T_kelvin, int kinds,

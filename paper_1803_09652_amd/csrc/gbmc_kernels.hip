@@ -2935,22 +2935,25 @@ __device__ __forceinline__ int sweep_proposal(const SiteDev& sd, int m, int s, c
 }
 
 constexpr int kCouple = 512;    // threads per pair of sites
+constexpr int kCoupleGroups = 1 << 20;  // most workgroups of a launch (below 2^32 threads)
 
 // couple[c_offset + i S + j] = dq_i . K . dq_j for sites i != j of a system of S
-// sites, and on the diagonal dq_i . phi_i + 1/2 dq_i . K . dq_i.
+// sites, and on the diagonal dq_i . phi_i + 1/2 dq_i . K . dq_i (sweep_live: the
+// diagonals alone, couple[m] of site m).
 template <typename T>
 __global__ __launch_bounds__(kCouple) void k_site_couple(
     SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
     const T* __restrict__ Q, const Row64* __restrict__ rows, double kC,
     double kT, double kO, double kap, double cut2, const unsigned long long* __restrict__ phi_fx,
     const int32_t* __restrict__ current_state, int kinds, const double* __restrict__ u,
-    double* __restrict__ couple)
+    double* __restrict__ couple, int first)
 {
     __shared__ double sx[2][kMaxSiteAtoms], sy[2][kMaxSiteAtoms], sz[2][kMaxSiteAtoms];
     __shared__ double sR[2][kMaxSiteAtoms], sA[2][kMaxSiteAtoms], sdq[2][kMaxSiteAtoms];
     __shared__ double red[1][kCouple / kTile];
     const int t = threadIdx.x;
-    const int m[2] = {sd.couples[2 * blockIdx.x], sd.couples[2 * blockIdx.x + 1]};
+    const int pair = first + blockIdx.x;
+    const int m[2] = {sd.couples ? sd.couples[2 * pair] : pair, sd.couples ? sd.couples[2 * pair + 1] : pair};
     const bool same = m[0] == m[1];
     if (!(kinds & (1 << sd.site_kind[m[0]])) || !(kinds & (1 << sd.site_kind[m[1]]))) return;
     double part[1] = {0.0};
@@ -3005,36 +3008,74 @@ __global__ __launch_bounds__(kCouple) void k_site_couple(
     block_sum<1, kCouple / kTile>(red, part);
     if (t == 0) {
         const int i = m[0] - s0, j = m[1] - s0;
-        c_out[(size_t)i * S + j] = part[0];
-        c_out[(size_t)j * S + i] = part[0];
+        if (sd.sweep_live) {
+            c_out[i] = part[0];
+        } else {
+            c_out[(size_t)i * S + j] = part[0];
+            c_out[(size_t)j * S + i] = part[0];
+        }
     }
 }
 
-constexpr int kSweep = 256;             // threads of the per-system sweep
 constexpr int kSweepCache = 64;         // sites of a system up to which its couplings fit in LDS
 
-template <typename T>
-__global__ __launch_bounds__(kSweep) void k_mc_sweep(
-    SiteDev sd, T* __restrict__ Qout, const double* __restrict__ couple,
+template <bool LIVE>
+constexpr int kSweep = LIVE ? 1024 : 256;   // threads of the per-system sweep
+
+// LDS of a sweep over systems of at most S sites and na site atoms.
+template <bool LIVE>
+size_t sweep_lds(size_t S, size_t na)
+{
+    const size_t c = std::min(S, (size_t)kSweepCache);
+    return (3 * 8 + 4 + 2 + 3) * S + (LIVE ? (7 * 8 + 2) * na : 8 * c * c);
+}
+
+// Without LIVE the couplings of all pairs of sites come from k_site_couple, and an
+// accepted visit adds a row of them.  Their number grows with the square of the sites
+// (a workgroup for each, 3.5 ns), so where the batch has more than kSweepPairs of
+// them per site of its largest system an accepted visit forms its row here, one site
+// atom per thread, for the sites not visited yet.  A whole sweep, couplings first / at
+// the visits, us, with a sixth and with all of the visits accepted:
+//   64 systems of 8 sites (288 pairs per site)    111 / 131,  115 / 155
+//   16 of 64 (520)      222 / 203,  233 / 376
+//   16 of 100 (808)     383 / 286,  425 / 830
+//   16 of 256 (2,056)  1686 / 420, 1820 / 1117
+template <typename T, bool LIVE>
+__global__ __launch_bounds__(kSweep<LIVE>) void k_mc_sweep(
+    SiteDev sd, const T* __restrict__ X, const T* __restrict__ Y, const T* __restrict__ Z,
+    const Row64* __restrict__ rows, double kC, double kT, double kO, double kap, double cut2,
+    T* __restrict__ Qout, const double* __restrict__ couple,
     int32_t* __restrict__ current_state, const double* __restrict__ pH,
     const double* __restrict__ E_volt, double T_kelvin, int kinds, const double* __restrict__ u,
     int32_t* __restrict__ n_electrons, int64_t* __restrict__ counters,
     int32_t* __restrict__ accepted, double* __restrict__ dG_out)
 {
-    extern __shared__ double sC[];
-    // per site: Delta G at the charges left so far, its value at the visit, the
-    // acceptance uniform; visiting order, current and proposed state, decision
-    __shared__ double dg[kMaxSweepSites], dg_at[kMaxSweepSites], su[kMaxSweepSites];
-    __shared__ int order[kMaxSweepSites];
-    __shared__ unsigned short site_of[kMaxSweepSites];
-    __shared__ unsigned char st[kMaxSweepSites], st_new[kMaxSweepSites], acc[kMaxSweepSites];
-    const int b = blockIdx.x, t = threadIdx.x;
+    extern __shared__ double s_mem[];
+    constexpr int W = kSweep<LIVE>;
+    const int b = blockIdx.x, t = threadIdx.x, wave = t / kTile, lane = t % kTile;
     const int s0 = sd.sys_site_offset[b], S = sd.sys_site_offset[b + 1] - s0;
+    const int sa0 = sd.sys_sa_offset[b], nsa = sd.sys_sa_offset[b + 1] - sa0;
+    // per site: Delta G at the charges left so far, its value at the visit, the
+    // acceptance uniform; visiting order, current and proposed state (the same for a
+    // site of a kind not swept), decision (bit 0) and whether it was visited (bit 1).
+    // Per site atom (LIVE): position, R, A, proposed change, coupling; its site
+    double* p = s_mem;
+    auto take = [&](int n) { double* q = p; p += n; return q; };
+    double *dg = take(S), *dg_at = take(S), *su = take(S);
+    double* sC = take(!LIVE && S <= kSweepCache ? S * S : 0);
+    const int na_lds = LIVE ? nsa : 0;
+    double *sx = take(na_lds), *sy = take(na_lds), *sz = take(na_lds), *sR = take(na_lds);
+    double *sA = take(na_lds), *sdq = take(na_lds), *sv = take(na_lds);
+    int* order = reinterpret_cast<int*>(p);
+    unsigned short* site_of = reinterpret_cast<unsigned short*>(order + S);
+    unsigned short* of_atom = site_of + S;
+    unsigned char* st = reinterpret_cast<unsigned char*>(of_atom + na_lds);
+    unsigned char *st_new = st + S, *acc = st_new + S;
     const double* C = couple + sd.sys_couple_offset[b];
     const double kTB = kKB * T_kelvin;
-    if (S <= kSweepCache)
-        for (int k = t; k < S * S; k += kSweep) sC[k] = C[k];
-    for (int i = t; i < S; i += kSweep) {
+    if (!LIVE && S <= kSweepCache)
+        for (int k = t; k < S * S; k += W) sC[k] = C[k];
+    for (int i = t; i < S; i += W) {
         const int m = s0 + i, s = current_state[m], kind = sd.site_kind[m];
         acc[i] = 0;
         st[i] = st_new[i] = (unsigned char)s;
@@ -3043,8 +3084,25 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
         const double drive = kind == 0 ? kKB * T_kelvin * kLn10 * pH[b] : kFaraday * E_volt[b];
         st_new[i] = (unsigned char)s_new;
         su[i] = u[3 * (size_t)m + 2];
-        dg[i] = C[(size_t)i * S + i] + drive * (double)(sd.state_count[g0 + s_new] - sd.state_count[g0 + s])
+        dg[i] = C[LIVE ? (size_t)i : (size_t)i * S + i]
+              + drive * (double)(sd.state_count[g0 + s_new] - sd.state_count[g0 + s])
               - (sd.state_gref[g0 + s_new] - sd.state_gref[g0 + s]);
+    }
+    if constexpr (LIVE) {
+        __syncthreads();
+        for (int i = wave; i < S; i += W / kTile) {
+            const int m = s0 + i, a0 = sd.site_atom_offset[m], na = sd.site_atom_offset[m + 1] - a0;
+            const int g0 = sd.site_state_offset[m];
+            const double* qn = sd.state_charges + sd.state_charge_offset[g0 + st_new[i]];
+            const double* qo = sd.state_charges + sd.state_charge_offset[g0 + st[i]];
+            for (int a = lane; a < na; a += kTile) {
+                const int l = a0 - sa0 + a, g = sd.site_atoms[a0 + a];
+                sx[l] = X[g]; sy[l] = Y[g]; sz[l] = Z[g];
+                sR[l] = rows[g].R; sA[l] = rows[g].A;
+                sdq[l] = qn[a] - qo[a];
+                of_atom[l] = (unsigned short)i;
+            }
+        }
     }
     for (int kind = 0; kind < 2; ++kind) {
         if (!(kinds & (1 << kind))) continue;
@@ -3055,14 +3113,14 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
         // rank of each site by (u[3m], m); a NaN key sorts last, so the ranks
         // always form a permutation
         // (a site's key waits in dg_at, which its visit overwrites)
-        for (int k = t; k < cnt; k += kSweep) {
+        for (int k = t; k < cnt; k += W) {
             const int m = list[k];
             const double key = u[3 * (size_t)m];
             dg_at[m - s0] = key == key ? key : 2.0;
             site_of[k] = m - s0;
         }
         __syncthreads();
-        for (int k = t; k < cnt; k += kSweep) {
+        for (int k = t; k < cnt; k += W) {
             const int i = site_of[k];
             const double key = dg_at[i];
             int rank = 0;
@@ -3080,33 +3138,54 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
             const bool yes = su[i] < exp(-d / kTB);
             if (t == 0) {
                 dg_at[i] = d;
-                acc[i] = yes;
+                acc[i] = 2 | yes;
             }
             if (!yes) continue;                         // the same for every thread
             // the other sites' Delta G at the charges this visit leaves
-            const double* row = (S <= kSweepCache ? sC : C) + (size_t)i * S;
             __syncthreads();
-            for (int k = t; k < S; k += kSweep)
-                if (k != i && (kinds & (1 << sd.site_kind[s0 + k]))) dg[k] += row[k];
+            if constexpr (LIVE) {
+                const int i0 = sd.site_atom_offset[s0 + i] - sa0, ni = sd.site_atom_offset[s0 + i + 1] - sa0;
+                for (int a = t; a < nsa; a += W) {
+                    const int k = of_atom[a];
+                    if (acc[k] || st_new[k] == st[k]) continue;
+                    double f = 0.0;
+                    for (int c = i0; c < ni; ++c)
+                        f = fma(sdq[c], pairK(sx[a] - sx[c], sy[a] - sy[c], sz[a] - sz[c], sR[a], sA[a], sR[c],
+                                              sA[c], kC, kT, kO, kap, cut2), f);
+                    sv[a] = sdq[a] * f;
+                }
+                __syncthreads();
+                for (int k = t; k < S; k += W) {
+                    if (acc[k] || st_new[k] == st[k]) continue;
+                    const int k0 = sd.site_atom_offset[s0 + k] - sa0, k1 = sd.site_atom_offset[s0 + k + 1] - sa0;
+                    double f = 0.0;
+                    for (int a = k0; a < k1; ++a) f += sv[a];
+                    dg[k] += f;
+                }
+            } else {
+                const double* row = (S <= kSweepCache ? sC : C) + (size_t)i * S;
+                for (int k = t; k < S; k += W)
+                    if (!acc[k] && st_new[k] != st[k]) dg[k] += row[k];
+            }
             __syncthreads();
         }
     }
     __syncthreads();
-    for (int i = t; i < S; i += kSweep) {
+    for (int i = t; i < S; i += W) {
         const int m = s0 + i;
-        if (!(kinds & (1 << sd.site_kind[m]))) continue;
-        if (accepted) accepted[m] = acc[i];
+        if (st_new[i] == st[i]) continue;
+        const int yes = acc[i] & 1;
+        if (accepted) accepted[m] = yes;
         if (dG_out) dG_out[m] = dg_at[i];
         if (counters) {
             counters[2 * (size_t)m] += 1;
-            counters[2 * (size_t)m + 1] += acc[i];
+            counters[2 * (size_t)m + 1] += yes;
         }
-        if (acc[i]) current_state[m] = st_new[i];
+        if (yes) current_state[m] = st_new[i];
     }
     // one wavefront per accepted site, and the electron count one redox site per thread
-    const int wave = t / kTile, lane = t % kTile;
-    for (int i = wave; i < S; i += kSweep / kTile) {
-        if (!acc[i]) continue;
+    for (int i = wave; i < S; i += W / kTile) {
+        if (!(acc[i] & 1)) continue;
         const int m = s0 + i, a0 = sd.site_atom_offset[m], na = sd.site_atom_offset[m + 1] - a0;
         const double* qn = sd.state_charges + sd.state_charge_offset[sd.site_state_offset[m] + st_new[i]];
         for (int a = lane; a < na; a += kTile) Qout[sd.site_atoms[a0 + a]] = (T)qn[a];
@@ -3116,7 +3195,7 @@ __global__ __launch_bounds__(kSweep) void k_mc_sweep(
         int ne = 0;
         for (int k = lane; k < nr; k += kTile) {
             const int m = sd.sys_redox_sites[r0 + k], i = m - s0;
-            ne += sd.state_count[sd.site_state_offset[m] + (acc[i] ? st_new[i] : st[i])];
+            ne += sd.state_count[sd.site_state_offset[m] + (acc[i] & 1 ? st_new[i] : st[i])];
         }
 #pragma unroll
         for (int off = kTile / 2; off > 0; off >>= 1) ne += __shfl_xor(ne, off);
@@ -3465,7 +3544,7 @@ hipError_t launch_mc_step(const SiteDev& sd, int n_sys, const T* x, const T* y, 
 }
 
 template <typename T>
-hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, const T* x, const T* y,
+hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, int max_site_atoms, const T* x, const T* y,
                            const T* z, const T* q, T* q_out, const GBConst& c, const Work<T>& w,
                            unsigned long long* phi_fx, double* couple, int32_t* current_state,
                            const double* pH, const double* E_volt, double T_kelvin, int kinds,
@@ -3479,14 +3558,16 @@ hipError_t launch_mc_sweep(const SiteDev& sd, int n_sys, int max_sites, const T*
         auto rows = c.kappa != 0.0 ? k_site_phi_rows<T, true> : k_site_phi_rows<T, false>;
         hipLaunchKernelGGL(rows, dim3(sd.n_rowitems), dim3(kTile), 0, s, sd.rowitems, sd.site_atoms, w.rows, q, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, w.ovf);
     }
-    if (sd.n_couples > 0)
-        hipLaunchKernelGGL(k_site_couple<T>, dim3(sd.n_couples), dim3(kCouple), 0, s, sd, x, y, z, q,
-                           w.rows, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), phi_fx, current_state,
-                           kinds, u, couple);
-    const size_t cached = (size_t)std::min(max_sites, kSweepCache);
-    hipLaunchKernelGGL(k_mc_sweep<T>, dim3(n_sys), dim3(kSweep), sizeof(double) * cached * cached, s, sd,
-                       q_out, couple, current_state, pH, E_volt, T_kelvin, kinds, u, n_electrons,
-                       counters, accepted, dG);
+    for (int first = 0; first < sd.n_couples; first += kCoupleGroups)
+        hipLaunchKernelGGL(k_site_couple<T>, dim3(std::min(sd.n_couples - first, kCoupleGroups)),
+                           dim3(kCouple), 0, s, sd, x, y, z, q, w.rows, c.kC, c.kT, c.kO, c.kappa,
+                           cut2_of(c), phi_fx, current_state, kinds, u, couple, first);
+    auto sweep = sd.sweep_live ? k_mc_sweep<T, true> : k_mc_sweep<T, false>;
+    hipLaunchKernelGGL(sweep, dim3(n_sys), dim3(sd.sweep_live ? kSweep<true> : kSweep<false>),
+                       sd.sweep_live ? sweep_lds<true>(max_sites, max_site_atoms)
+                                     : sweep_lds<false>(max_sites, max_site_atoms),
+                       s, sd, x, y, z, w.rows, c.kC, c.kT, c.kO, c.kappa, cut2_of(c), q_out, couple,
+                       current_state, pH, E_volt, T_kelvin, kinds, u, n_electrons, counters, accepted, dG);
     return hipGetLastError();
 }
 
@@ -3526,7 +3607,7 @@ hipError_t launch_remd_exchange(int M, const double* E_rung, const int32_t* Ne, 
                                           const double*, const double*, double, const double*,   \
                                           const double*, const double*, int32_t*, int64_t*,      \
                                           int32_t*, hipStream_t, hipEvent_t*);                   \
-    template hipError_t launch_mc_sweep<T>(const SiteDev&, int, int, const T*, const T*,          \
+    template hipError_t launch_mc_sweep<T>(const SiteDev&, int, int, int, const T*, const T*,          \
                                            const T*, const T*, T*, const GBConst&,               \
                                            const Work<T>&, unsigned long long*, double*, int32_t*, \
                                            const double*, const double*, double, int,            \
