@@ -61,12 +61,13 @@ def _f64p(a: np.ndarray):
     return a.ctypes.data_as(C.POINTER(C.c_double))
 
 
-# the library's default work shapes (radii, energy, chain) per precision
-# The library's default shapes for batches below its long-item size (a plan
-# created without either knob takes the library's own choice, which for FP32
-# batches of at least 2^19 tiles walks four j blocks per item with one wave per
-# workgroup in the energy and chain passes); a knob left None when the other
-# is given takes the value below.
+# The library's default shapes (radii, energy, chain) for batches below its long-item
+# size.  A plan created without either knob takes the library's own choice, which
+# for FP32 batches of at least 2^19 tiles walks four j blocks per item with one
+# wave per workgroup in the energy and chain passes, and in passes of few items
+# shares the steps of an item among the waves of a workgroup, which no explicit
+# shape does, these values included; a knob left None when the other is given
+# takes the value below.
 DEFAULT_SHAPE = {"fp32": {"j_blocks_per_item": (1, 1, 1), "waves_per_group": (2, 4, 4)},
                  "fp64": {"j_blocks_per_item": (1, 1, 1), "waves_per_group": (2, 2, 2)}}
 
@@ -76,6 +77,9 @@ def _per_pass(v, default):
         return tuple(default)
     if isinstance(v, (int, np.integer)):
         return (int(v),) * L.N_PASSES
+    v = tuple(v)
+    if len(v) == L.N_PASSES and all(x is None for x in v):
+        return tuple(default)
     v = tuple(int(x) for x in v)
     if len(v) != L.N_PASSES:
         raise ValueError("give one value, or one per pass (radii, energy, chain)")
@@ -85,7 +89,7 @@ def _per_pass(v, default):
 def tuning_struct(j_blocks_per_item=None, waves_per_group=None,
                   precision: str = "fp32") -> L.gbmc_tuning:
     """Work shape per pair pass; each argument is an int (all passes) or a
-    (radii, energy, chain) triple; None keeps the library default."""
+    (radii, energy, chain) triple; None (or a triple of it) takes DEFAULT_SHAPE."""
     jb = _per_pass(j_blocks_per_item, DEFAULT_SHAPE[precision]["j_blocks_per_item"])
     wv = _per_pass(waves_per_group, DEFAULT_SHAPE[precision]["waves_per_group"])
     t = L.gbmc_tuning()
@@ -99,7 +103,9 @@ class Plan:
     """A batch layout (systems back to back) and a precision.
 
     precision: "fp32" (FP32 pair arithmetic, 64-bit fixed-point sums) or
-    "fp64".  Owns the plan's device workspace."""
+    "fp64".  j_blocks_per_item, waves_per_group: work shape (see tuning_struct); both
+    None, or triples of it, leave the choice to the library.  Owns the plan's device
+    workspace."""
 
     single_launch = False       # see set_single_launch
 
@@ -116,7 +122,9 @@ class Plan:
         self.device = torch.device("cuda", torch.cuda.current_device()) if device is None \
             else torch.device(device)
         tun = None
-        if j_blocks_per_item is not None or waves_per_group is not None:
+        none = lambda v: v is None or (isinstance(v, (tuple, list)) and len(v) == L.N_PASSES
+                                       and all(x is None for x in v))
+        if not (none(j_blocks_per_item) and none(waves_per_group)):
             tun = C.byref(tuning_struct(j_blocks_per_item, waves_per_group, precision))
         h = C.c_void_p()
         with torch.cuda.device(self.device):

@@ -4,8 +4,10 @@ The two knobs of ``gbmc_tuning`` (j blocks walked per work item, independent
 wavefronts per workgroup) change only the schedule, never the result (every
 64 x 64 tile is rounded into fixed point on its own), so the tuner can pick
 them by timing alone.  It times the three pair kernels with the library's HIP
-event hook on the caller's actual batch and keeps the fastest shape.  Results
-are cached in a JSON file keyed by precision and a size bucket of the batch.
+event hook on the caller's actual batch and keeps the fastest shape, or none:
+without a shape the library's own choice runs passes of few items with a
+workgroup for each, which no shape asks for.  Results are cached in a JSON
+file keyed by precision and a size bucket of the batch.
 """
 from __future__ import annotations
 
@@ -26,6 +28,8 @@ PAIR_KERNELS = ("radii_pairs", "energy_pairs", "chain_pairs")
 
 _CACHE_ENV = "GBMC_TUNING_CACHE"
 
+UNTUNED = (None,) * len(PAIR_KERNELS)       # of both knobs: the library's own choice
+
 
 def cache_path() -> str:
     return os.environ.get(_CACHE_ENV,
@@ -34,12 +38,13 @@ def cache_path() -> str:
 
 def bucket_key(atom_offset: Sequence[int], precision: str) -> str:
     """Size bucket of a batch: system count and largest system (powers of two)
-    plus the total number of 64 x 64 tiles (powers of two)."""
+    plus the total number of 64 x 64 tiles (powers of two); version 2: entries
+    picked with the untuned plan among the candidates."""
     n = np.diff(np.asarray(atom_offset, dtype=np.int64))
     nb = (n + 63) // 64
     tiles = int((nb * (nb + 1) // 2).sum())
     lg = lambda v: int(math.ceil(math.log2(max(1, v))))
-    return f"{precision}:B{lg(len(n))}:N{lg(int(n.max()) if n.size else 1)}:T{lg(tiles)}"
+    return f"{precision}:B{lg(len(n))}:N{lg(int(n.max()) if n.size else 1)}:T{lg(tiles)}:2"
 
 
 def _load_cache() -> dict:
@@ -63,7 +68,8 @@ def _save_cache(cache: dict) -> None:
 
 
 def lookup(atom_offset: Sequence[int], precision: str = "fp32"):
-    """Cached (j_blocks_per_item, waves_per_group) triples for this size bucket, or None."""
+    """Cached (j_blocks_per_item, waves_per_group) triples for this size bucket (of None
+    where the untuned plan was fastest), or None."""
     hit = _load_cache().get(bucket_key(atom_offset, precision))
     return (tuple(hit["j_blocks_per_item"]), tuple(hit["waves_per_group"])) if hit else None
 
@@ -73,12 +79,15 @@ def tune(batch, precision: str = "fp32", order: Optional[np.ndarray] = None,
          candidates: Optional[Iterable[Tuple[int, int]]] = None, use_cache: bool = True) -> dict:
     """Time every (j_blocks_per_item, waves_per_group) candidate on ``batch``
     (any object with atom_offset, x, y, z, q, rho, screen), applied to all three
-    pair passes, and pick the fastest shape of each pass.  Returns
-    {"best": ((jb radii, energy, chain), (wv radii, energy, chain)), ...}."""
+    pair passes, and pick the fastest shape of each pass.  Without a list of
+    candidates the untuned plan is one too, for all passes together ("default").  Returns
+    {"best": ((jb radii, energy, chain), (wv radii, energy, chain)), ...}, both
+    (None, None, None) where the untuned plan is as fast; Plan() takes either."""
     key = bucket_key(batch.atom_offset, precision)
     cands = list(candidates) if candidates is not None else [(j, w) for j in J_BLOCKS for w in WAVES]
     table, per_kernel = {}, {}
-    for jb, wv in cands:
+    for jb, wv in cands + ([(None, None)] if candidates is None else []):
+        name = "default" if jb is None else f"{jb}x{wv}"
         plan = api.Plan(batch.atom_offset, precision, j_blocks_per_item=jb, waves_per_group=wv)
         if order is not None:
             plan.set_order(order)
@@ -95,21 +104,26 @@ def tune(batch, precision: str = "fp32", order: Optional[np.ndarray] = None,
             for k in PAIR_KERNELS:
                 per[k].append(ms.get(k, 0.0))
         plan.set_timing(False)
-        table[f"{jb}x{wv}"] = statistics.median(runs)
-        per_kernel[f"{jb}x{wv}"] = {k: statistics.median(v) for k, v in per.items()}
+        table[name] = statistics.median(runs)
+        per_kernel[name] = {k: statistics.median(v) for k, v in per.items()}
         del plan, atoms
     torch.cuda.synchronize()
     # the passes are separate launches: each takes its own fastest shape
     jbs, wvs, total = [], [], 0.0
     for k in PAIR_KERNELS:
-        shape = min(per_kernel, key=lambda c: per_kernel[c][k])
+        shape = min((c for c in per_kernel if c != "default"), key=lambda c: per_kernel[c][k])
         jb, wv = (int(v) for v in shape.split("x"))
         jbs.append(jb)
         wvs.append(wv)
         total += per_kernel[shape][k]
     best = (tuple(jbs), tuple(wvs))
+    if "default" in per_kernel:
+        untuned = sum(per_kernel["default"].values())
+        if untuned <= total:
+            best, total = (UNTUNED, UNTUNED), untuned
     if use_cache:
         cache = _load_cache()
-        cache[key] = {"j_blocks_per_item": list(jbs), "waves_per_group": list(wvs), "pair_ms": total}
+        cache[key] = {"j_blocks_per_item": list(best[0]), "waves_per_group": list(best[1]),
+                      "pair_ms": total}
         _save_cache(cache)
     return {"key": key, "best": best, "pair_ms": total, "ms": table, "per_kernel_ms": per_kernel}

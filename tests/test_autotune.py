@@ -54,3 +54,57 @@ def test_tune_picks_a_candidate_per_pass_and_keeps_results(tmp_path, monkeypatch
     torch.cuda.synchronize()
     for k in ("R", "Ec", "Egb", "force", "dEdq", "dEdrho"):
         assert np.array_equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("untuned,best", [(0.5, ((None,) * 3, (None,) * 3)), (2.5, ((1, 2, 1), (4, 1, 2)))])
+def test_tune_weighs_the_untuned_plan(tmp_path, monkeypatch, untuned, best):
+    # the plan without a shape takes kernels that no shape asks for: it is a candidate
+    # of its own, and wins where it is faster than the best shapes together (0.6 each)
+    from types import SimpleNamespace
+    monkeypatch.setenv("GBMC_TUNING_CACHE", str(tmp_path / "tuning.json"))
+    fast = {"radii_pairs": (1, 4), "energy_pairs": (2, 1), "chain_pairs": (1, 2)}
+
+    class Plan:
+        def __init__(self, off, prec, j_blocks_per_item=None, waves_per_group=None):
+            self.shape = (j_blocks_per_item, waves_per_group)
+
+        def set_timing(self, on):
+            pass
+
+        def kernel_ms(self):
+            if self.shape == (None, None):
+                return {k: untuned for k in at.PAIR_KERNELS}
+            return {k: 0.6 if self.shape == s else 1.0 for k, s in fast.items()}
+    monkeypatch.setattr(at.api, "Plan", Plan)
+    monkeypatch.setattr(at.api, "Atoms", SimpleNamespace(from_batch=lambda plan, batch: None))
+    for name in ("radii", "energy_forces"):
+        monkeypatch.setattr(at.api, name, lambda *a: None)
+    monkeypatch.setattr(at.torch.cuda, "synchronize", lambda: None)
+    batch = SimpleNamespace(atom_offset=np.array([0, 256]))
+    r = at.tune(batch)
+    assert r["best"] == best == at.lookup(batch.atom_offset)
+    assert r["pair_ms"] == pytest.approx(min(3 * untuned, 1.8)) and r["ms"]["default"] == pytest.approx(3 * untuned)
+    # with a list of candidates the choice stays inside it
+    assert at.tune(batch, candidates=[(1, 2)], use_cache=False)["best"] == ((1,) * 3, (2,) * 3)
+
+
+@pytest.mark.gpu
+def test_tuned_small_plan_is_not_slower_than_an_untuned_one(tmp_path, monkeypatch):
+    # a triple of None is no shape at all: the tuner's result for a small batch makes the
+    # plan that runs one workgroup per item (kernel times of 256 atoms: about half)
+    import synth
+    from gpu_common import build, gb, params_pair
+    monkeypatch.setenv("GBMC_TUNING_CACHE", str(tmp_path / "tuning.json"))
+    systems = synth.globule_256()
+    batch = synth.make_batch(systems)
+    r = at.tune(batch, "fp32", reps=3)
+    assert r["best"] == ((None,) * 3, (None,) * 3)
+    g, ms = gb(), {}
+    for name, (jb, wv) in (("tuned", r["best"]), ("walk", ((1, 1, 1), (2, 4, 4)))):
+        _, _, plan, atoms = build(systems, "fp32", j_blocks=jb, waves=wv)
+        g.evaluate(plan, atoms, params_pair()[0])
+        plan.set_timing(True)
+        for _ in range(20):
+            g.evaluate(plan, atoms, params_pair()[0])
+        ms[name] = sum(plan.kernel_ms().values())
+    assert ms["tuned"] < 0.8 * ms["walk"], ms
