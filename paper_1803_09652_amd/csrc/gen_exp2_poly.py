@@ -1,6 +1,9 @@
 """Generate exp2_poly.inc: 2^f on -1/2 <= f <= 1/2 in double precision, the
 reduced argument of the FP64 kernels' exponential.  Degree 11, relative-weighted
-least squares at Chebyshev nodes in mpmath."""
+least squares at Chebyshev nodes in mpmath, rounded one coefficient after the other
+from the constant up, the rest fitted anew to what the rounded ones leave (with
+fused operations, largest and mean errors of 1.05 and 0.37 units of 2^-53;
+rounded all at once 1.26 and 0.38; of the rounded function itself 1.00 and 0.36)."""
 import os
 
 import mpmath
@@ -13,15 +16,16 @@ def fit(deg):
     mpmath.mp.dps = 50
     m = 200
     xs = [mpmath.cos(mpmath.pi * (k + mpmath.mpf(1) / 2) / m) / 2 for k in range(m)]
-    A = mpmath.matrix(m, deg + 1)
-    b = mpmath.matrix(m, 1)
-    for i, x in enumerate(xs):
-        f = mpmath.power(2, x)
-        for j in range(deg + 1):
-            A[i, j] = x ** j / f
-        b[i] = 1
-    c = mpmath.lu_solve(A.T * A, A.T * b)
-    return [c[j] for j in range(deg + 1)]
+    fs = [mpmath.power(2, x) for x in xs]
+    done = []
+    while len(done) <= deg:
+        A, b = mpmath.matrix(m, deg + 1 - len(done)), mpmath.matrix(m, 1)
+        for i, (x, f) in enumerate(zip(xs, fs)):
+            for j in range(len(done), deg + 1):
+                A[i, j - len(done)] = x ** j / f
+            b[i] = 1 - mpmath.fsum(mpmath.mpf(c) * x ** j for j, c in enumerate(done)) / f
+        done.append(float(mpmath.lu_solve(A.T * A, A.T * b)[0]))
+    return done
 
 
 def horner_error(c):

@@ -52,3 +52,21 @@ def test_fit_meets_its_stated_error(name, far):
     # half a unit in the last place of a value just above a power of two, and
     # another of the last product and sum
     assert err <= max(FAR[far][2], 2.0 ** -23 if ctype == "float" else 2.0 ** -52)
+
+
+def test_fp64_fit_is_no_less_accurate_than_the_one_it_replaces():
+    # with fused operations, as the kernels evaluate both: largest and mean errors on the
+    # domain, in exact arithmetic
+    from fractions import Fraction
+
+    def errors(coef, ys):
+        out = []
+        for y in ys:
+            p = coef[0]
+            for v in coef[1:]:
+                p = float(Fraction(p) * Fraction(y) + Fraction(v))      # one rounding
+            out.append(abs(float(mpmath.mpf(p) / exact("P", y) - 1)))
+        return max(out), sum(out) / len(out)
+    ys = [float(v) for v in np.random.default_rng(0).uniform(0.0, VFAR["hct_poly64_vfar"][1], 1500)]
+    new, old = (errors(f[4], ys) for f in (VFAR["hct_poly64_vfar"], FAR["hct_poly64_far"]))
+    assert new[0] <= old[0] and new[1] <= old[1], (new, old)
