@@ -85,7 +85,6 @@ struct gbmc_plan {
     WorkItem* d_near[GBMC_N_PASSES] = {nullptr, nullptr, nullptr};   // in the order of near_first
     void* d_mem = nullptr;           // one allocation: the work lists and the order
     int32_t* d_perm = nullptr;       // [N] internal -> caller atom index
-    int32_t* d_offset = nullptr;     // [B+1] device copy of the atom offsets
     int32_t n_blocks = 0;            // 64-atom blocks of the batch
     BlockSpan* d_blocks = nullptr;   // [n_blocks] atoms of each block (processing order)
     int32_t* d_total = nullptr;      // [3][n_blocks] items of each pass touching each block
@@ -257,7 +256,6 @@ static Work<T> carve(const gbmc_plan* p, void* ws)
     char* b = static_cast<char*>(ws);
     Work<T> w;
     w.perm = p->d_perm;
-    w.atom_offset = p->d_offset;
     w.P = reinterpret_cast<Q4<T>*>(b + p->off_P);
     w.Gx = reinterpret_cast<Q4<T>*>(b + p->off_Gx);
     w.I_fx = reinterpret_cast<unsigned long long*>(b + p->off_I);
@@ -585,9 +583,7 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
             o = align256(o + near[k].size() * sizeof(WorkItem));
         }
         at[GBMC_N_PASSES] = o;
-        const size_t off_bytes = 4 * (size_t)(n_systems + 1);
-        const size_t at_off = align256(o + 4 * (size_t)p->n_atoms);
-        const size_t at_blk = align256(at_off + off_bytes);
+        const size_t at_blk = align256(o + 4 * (size_t)p->n_atoms);
         const size_t at_chk = align256(at_blk + sizeof(BlockSpan) * blocks.size());
         const size_t at_tot = align256(at_chk + sizeof(WorkItem) * chunks.size());
         const size_t at_sum = align256(at_tot + sizeof(int32_t) * totals.size());
@@ -609,8 +605,6 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
             p->d_perm = reinterpret_cast<int32_t*>(d + at[GBMC_N_PASSES]);
             int32_t* id = reinterpret_cast<int32_t*>(h.data() + at[GBMC_N_PASSES]);
             for (int32_t k = 0; k < p->n_atoms; ++k) id[k] = k;
-            p->d_offset = reinterpret_cast<int32_t*>(d + at_off);
-            std::memcpy(h.data() + at_off, p->offset.data(), off_bytes);
             p->d_blocks = reinterpret_cast<BlockSpan*>(d + at_blk);
             if (!blocks.empty())
                 std::memcpy(h.data() + at_blk, blocks.data(), sizeof(BlockSpan) * blocks.size());

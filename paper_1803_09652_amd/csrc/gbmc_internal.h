@@ -105,7 +105,6 @@ struct Work {
     unsigned long long* phi_fx;   // [N] internal
     unsigned long long* drho_fx;  // [N] internal
     unsigned long long* EA_fx;    // [2][N] internal: per-atom Coulomb and GB energy shares
-    const int32_t* atom_offset;   // [B+1] (plan memory)
     Row64* rows;                  // [N] FP64 state of every atom
     double* dRdPsi_p;             // [N] internal: dR/dPsi in processing order (the chain
                                   //  pass forms B rt from it and G_fx)

@@ -294,29 +294,6 @@ __device__ __forceinline__ void dist64(double xi, double yi, double zi, double x
     r = r2 * invr;
 }
 
-// Pass-1 pair: H(r; rt_i, S_j) and H(r; rt_j, S_i).
-// FP32: non-overlapping pairs (r - S >= rt, x = S/r with x^2 <= YMAX) use
-// H = x^3 P(x^2) / r; every other pair takes hct_slow32.
-__device__ __forceinline__ void radii_pair(float xi, float yi, float zi, float xj, float yj, float zj,
-                                           float rti, float Si, float rtj, float Sj, float& hij,
-                                           float& hji)
-{
-    float dx = xi - xj, dy = yi - yj, dz = zi - zj;
-    float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    float invr = rsq(r2);
-    float r = r2 * invr;
-    float xij = Sj * invr, yij = xij * xij;
-    float xji = Si * invr, yji = xji * xji;
-    hij = xij * yij * invr * hct_poly(yij);
-    hji = xji * yji * invr * hct_poly(yji);
-    bool f_ij = (r - Sj >= rti) & (yij <= GBMC_HCT_YMAX);
-    bool f_ji = (r - Si >= rtj) & (yji <= GBMC_HCT_YMAX);
-    if (!(f_ij & f_ji)) {
-        if (!f_ij) hij = hct_slow32<false>(r, invr, rti, Sj, nullptr);
-        if (!f_ji) hji = hct_slow32<false>(r, invr, rtj, Si, nullptr);
-    }
-}
-
 // Tiers of a tile, from the gap between its blocks (tile_tier): 0 some pair may
 // overlap; 1 all pairs take the polynomial form with y <= YFAR; 2 with y <= YVFAR.
 // Each tier takes the shortest fits that are as accurate as those of the tier
@@ -332,9 +309,11 @@ __device__ __forceinline__ double tier_p(double y)
     return TIER == 0 ? hct_poly64(y) : TIER == 1 ? hct_poly64_far(y) : hct_poly64_vfar(y);
 }
 
-// The polynomial form alone, for walks that defer the pairs it does not cover
-// (as chain_pair_fast): a pair that needs the closed form in either direction
-// gets zero terms and, if act, its bit in mask.
+// Pass-1 pair: H(r; rt_i, S_j) and H(r; rt_j, S_i) by the polynomial form alone,
+// H = x^3 P(x^2) / r with x = S/r (non-overlapping pairs, r - S >= rt, x^2 <= YMAX),
+// for walks that defer the pairs it does not cover (as chain_pair_fast): a pair
+// that needs the closed form in either direction gets zero terms and, if act, its
+// bit in mask.
 template <int TIER>
 __device__ __forceinline__ void radii_pair_fast(float xi, float yi, float zi, float xj, float yj,
                                                 float zj, float rti, float Si, float rtj, float Sj,
@@ -363,71 +342,13 @@ __device__ __forceinline__ void radii_pair_fast(float xi, float yi, float zi, fl
     }
 }
 
-// FP64: the same split, with a degree-14 polynomial on y <= 0.25 (one ulp);
-// every other pair takes the closed form.
-__device__ __forceinline__ void radii_pair(double xi, double yi, double zi, double xj, double yj,
-                                           double zj, double rti, double Si, double rtj, double Sj,
-                                           double& hij, double& hji)
-{
-    double r, invr;
-    dist64(xi, yi, zi, xj, yj, zj, r, invr);
-    const double xij = Sj * invr, yij = xij * xij;
-    const double xji = Si * invr, yji = xji * xji;
-    hij = xij * yij * invr * hct_poly64(yij);
-    hji = xji * yji * invr * hct_poly64(yji);
-    const bool f_ij = (r - Sj >= rti) & (yij <= GBMC_HCT_YMAX64);
-    const bool f_ji = (r - Si >= rtj) & (yji <= GBMC_HCT_YMAX64);
-    if (!(f_ij & f_ji)) {
-        if (!f_ij) hij = hct_general(r, invr, rti, Sj);
-        if (!f_ji) hji = hct_general(r, invr, rtj, Si);
-    }
-}
-
 // Pass-3 pair terms with the Born chain weights bi = B_i rt_i, bj = B_j rt_j
-// applied: dEdr = bi dH(r; rt_i, S_j)/dr + bj dH(r; rt_j, S_i)/dr, the S
-// derivatives gij2 = dH(r; rt_i, S_j)/dS and gji2 = dH(r; rt_j, S_i)/dS, and
-// the rt derivatives, nonzero only for overlapping pairs, added as
-// dri += bi dH(r; rt_i, S_j)/drt and drj += bj dH(r; rt_j, S_i)/drt.
-// FP32: non-overlapping directions use the polynomial form,
+// applied: dEdr = bi dH(r; rt_i, S_j)/dr + bj dH(r; rt_j, S_i)/dr and the S
+// derivatives gij2 = dH(r; rt_i, S_j)/dS and gji2 = dH(r; rt_j, S_i)/dS, by the
+// polynomial form alone, for walks that defer the pairs it does not cover:
 //   dH/dr = -x^3 (P + (1 - y)^-2) / r^2,  dH/dS = y (1 - y)^-2 / r^2,
-// with the common 1/r^2 of the two dH/dr applied once.
-__device__ __forceinline__ void chain_pair(float r, float r2, float invr, float rti, float Si,
-                                           float rtj, float Sj, float bi, float bj, float& dEdr,
-                                           float& gij2, float& gji2, float& dri, float& drj)
-{
-    const float u = invr * invr;
-    const float xij = Sj * invr, yij = xij * xij;
-    const float xji = Si * invr, yji = xji * xji;
-    float wij = rcp(1.0f - yij), wji = rcp(1.0f - yji);
-    wij *= wij;
-    wji *= wji;
-    // -r^2 dH/dr = x^3 (P + w) = x (y P + t), r^2 dH/dS = t = y w
-    const float tij = yij * wij, tji = yji * wji;
-    float aij = xij * fmaf(yij, hct_poly_d(yij), tij);
-    float aji = xji * fmaf(yji, hct_poly_d(yji), tji);
-    gij2 = tij * u;
-    gji2 = tji * u;
-    const bool f_ij = (r - Sj >= rti) & (yij <= GBMC_HCT_YMAX);
-    const bool f_ji = (r - Si >= rtj) & (yji <= GBMC_HCT_YMAX);
-    if (!(f_ij & f_ji)) {
-        float g[3];
-        if (!f_ij) {
-            hct_slow32<true>(r, invr, rti, Sj, g);
-            aij = -g[0] * r2;
-            gij2 = g[2];
-            dri = fmaf(bi, g[1], dri);
-        }
-        if (!f_ji) {
-            hct_slow32<true>(r, invr, rtj, Si, g);
-            aji = -g[0] * r2;
-            gji2 = g[2];
-            drj = fmaf(bj, g[1], drj);
-        }
-    }
-    dEdr = -u * fmaf(bi, aij, bj * aji);
-}
-
-// The polynomial form alone, for walks that defer the pairs it does not cover.
+// with the common 1/r^2 of the two dH/dr applied once (-r^2 dH/dr = x (y P + t),
+// r^2 dH/dS = t = y (1 - y)^-2).
 // A pair that needs the closed form in either direction (act only) gets zero
 // terms and its bit in mask (one wave-uniform branch, taken only in the steps
 // that meet such a pair); the caller evaluates those pairs after the walk.
@@ -472,43 +393,6 @@ __device__ __forceinline__ void chain_pair_fast(float r, float invr, float rti, 
         mask |= (!fast && act) ? bit : 0ull;
     }
     dEdr = -u * fmaf(bi, aij, bj * aji);
-}
-
-// FP64: the same split with the FP64 polynomial; overlapping pairs take the
-// closed-form partials.
-__device__ __forceinline__ void chain_pair(double r, double r2, double invr, double rti, double Si,
-                                           double rtj, double Sj, double bi, double bj,
-                                           double& dEdr, double& gij2, double& gji2, double& dri,
-                                           double& drj)
-{
-    const double u = invr * invr;
-    const double xij = Sj * invr, yij = xij * xij;
-    const double xji = Si * invr, yji = xji * xji;
-    double wij = rcp64(1.0 - yij), wji = rcp64(1.0 - yji);
-    wij *= wij;
-    wji *= wji;
-    double aij = xij * yij * (hct_poly64(yij) + wij);    // -r^2 dH/dr
-    double aji = xji * yji * (hct_poly64(yji) + wji);
-    gij2 = yij * wij * u;
-    gji2 = yji * wji * u;
-    const bool f_ij = (r - Sj >= rti) & (yij <= GBMC_HCT_YMAX64);
-    const bool f_ji = (r - Si >= rtj) & (yji <= GBMC_HCT_YMAX64);
-    if (!(f_ij & f_ji)) {
-        double g0, g1, g2;
-        if (!f_ij) {
-            hct_general_grad(r, invr, rti, Sj, g0, g1, g2);
-            aij = -g0 * r2;
-            gij2 = g2;
-            dri = fma(bi, g1, dri);
-        }
-        if (!f_ji) {
-            hct_general_grad(r, invr, rtj, Si, g0, g1, g2);
-            aji = -g0 * r2;
-            gji2 = g2;
-            drj = fma(bj, g1, drj);
-        }
-    }
-    dEdr = -u * fma(bi, aij, bj * aji);
 }
 
 // FP64 forms of the two deferring pair functions (polynomial of degree 14 on
@@ -651,8 +535,10 @@ __device__ __forceinline__ void radii_pair_cut(double xi, double yi, double zi, 
     hji = out_ji ? 0.0 : hji;
 }
 
-// Pass-3 pair terms of H_c (see chain_pair): the c term contributes to the r
-// and S partials, not to the rt partial.
+// Pass-3 pair terms of H_c (see chain_pair_fast), and the rt derivatives, nonzero
+// only for overlapping pairs, added as dri += bi dH(r; rt_i, S_j)/drt and
+// drj += bj dH(r; rt_j, S_i)/drt: the c term contributes to the r and S
+// partials, not to the rt partial.
 __device__ __forceinline__ void chain_pair_cut(float r, float r2, float invr, float rti, float Si,
                                                float rtj, float Sj, float bi, float bj, float c,
                                                float& dEdr, float& gij2, float& gji2, float& dri,
