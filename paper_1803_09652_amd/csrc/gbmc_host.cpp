@@ -95,6 +95,7 @@ struct gbmc_plan {
     WorkItem* d_chunks = nullptr;
     int32_t n_sums = 0;              // spans of the energy sums
     SumSpan* d_sums = nullptr;       // [n_sums], then the same systems as one span each [n_sys]
+    bool sums_by_wave = false;
     int device = 0;
     void* scratch = nullptr;         // the library's static scratch on `device`
     hipError_t scratch_err = hipSuccess;
@@ -557,6 +558,9 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
             blk0 += (a1 - a0 + kTile - 1) / kTile;
         }
         p->n_sums = (int32_t)sums.size();
+        p->sums_by_wave = true;
+        for (const SumSpan& sp : whole)
+            p->sums_by_wave = p->sums_by_wave && sp.a1 - sp.a0 <= kSumWaveAtoms;
         sums.insert(sums.end(), whole.begin(), whole.end());
         p->n_chunks = (int32_t)chunks.size();
         p->cut_cap = p->n_chunks * (kCutChunk / kCutTiles);
@@ -871,7 +875,7 @@ static hipError_t run_queued(gbmc_plan* p, const gbmc_atoms* a, const GBConst& c
     int n = 0;
     for (int k = 0; k < GBMC_N_PASSES; ++k) n += p->n_items[k];
     hipEvent_t* ev = n > 0 ? events(p, {id}) : nullptr;
-    return launch_queued<T>(queue_shape(p), p->n_atoms, p->d_sums + p->n_sums, p->n_sys,
+    return launch_queued<T>(queue_shape(p), p->n_atoms, SumList{p->d_sums + p->n_sums, p->n_sys, p->sums_by_wave},
                             (const T*)a->x, (const T*)a->y,
                             (const T*)a->z, (const T*)a->q, (const T*)a->rho,
                             (const T*)a->screen, c, carve<T>(p, ws), (T*)born_R, e_coul, e_gb,
@@ -914,15 +918,16 @@ static hipError_t energy_launch(gbmc_plan* p, const gbmc_atoms* a, const GBConst
     if (p->n_items[GBMC_PASS_ENERGY] > 0)
         ev = chain ? events(p, {kKEnergy, kKChain}) : events(p, {kKEnergy});
     const PassShape pe = pass_shape(p, GBMC_PASS_ENERGY), pc = pass_shape(p, GBMC_PASS_CHAIN);
+    const SumList sums{p->d_sums, p->n_sums, p->sums_by_wave};
     if (p->prec == GBMC_FP32_FIXED)
-        return launch_energy_forces<float>(pe, pc, p->n_atoms, p->d_sums, p->n_sums, cut_plan(p),
+        return launch_energy_forces<float>(pe, pc, p->n_atoms, sums, cut_plan(p),
                                            (const float*)a->x, (const float*)a->y,
                                            (const float*)a->z, (const float*)a->q,
                                            (const float*)a->rho, (const float*)a->screen, c,
                                            carve<float>(p, ws), e_coul, e_gb, (float*)force,
                                            (float*)dEdq, (float*)dEdrho, s, ev, staged, finalize,
                                            (float*)born_R);
-    return launch_energy_forces<double>(pe, pc, p->n_atoms, p->d_sums, p->n_sums, cut_plan(p),
+    return launch_energy_forces<double>(pe, pc, p->n_atoms, sums, cut_plan(p),
                                         (const double*)a->x, (const double*)a->y,
                                         (const double*)a->z, (const double*)a->q,
                                         (const double*)a->rho, (const double*)a->screen, c,

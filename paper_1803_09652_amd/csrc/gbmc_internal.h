@@ -63,6 +63,14 @@ struct SumSpan {
     int32_t sys, a0, a1, n, slot;
 };
 constexpr int kSumAtoms = 4096;
+// Where no span has more atoms than this, every wavefront sums one.
+constexpr int kSumWaveAtoms = 256;
+struct SumList {
+    const SumSpan* spans;
+    int n;
+    bool by_wave;
+    int groups() const { return by_wave ? (n + 3) / 4 : n; }    // of 256 threads
+};
 
 // Static tables of the cutoff passes: the 64-atom blocks of the batch and the
 // chunks of 64 j blocks of every block row that the compaction kernel scans.
@@ -223,7 +231,7 @@ hipError_t launch_radii(const PassShape& radii, int n_atoms, const CutPlan& cp,
                         hipEvent_t* ev, const T* q = nullptr, bool finalize = true);
 template <typename T>
 hipError_t launch_energy_forces(const PassShape& energy, const PassShape& chain, int n_atoms,
-                                const SumSpan* sums, int n_sums, const CutPlan& cp,
+                                const SumList& sums, const CutPlan& cp,
                                 const T* x, const T* y, const T* z, const T* q, const T* rho,
                                 const T* screen, const GBConst& c, const Work<T>& w,
                                 double* e_coul, double* e_gb, T* force, T* dEdq, T* dEdrho,
@@ -250,7 +258,7 @@ struct QueueShape {
 // Staging, the three all-pairs passes (descreening, energy / explicit
 // forces with gradients, Born chain) in one queued launch, and the outputs.
 template <typename T>
-hipError_t launch_queued(const QueueShape& sh, int n_atoms, const SumSpan* sums, int n_sums,
+hipError_t launch_queued(const QueueShape& sh, int n_atoms, const SumList& sums,
                          const T* x, const T* y,
                          const T* z, const T* q, const T* rho, const T* screen, const GBConst& c,
                          const Work<T>& w, T* born_R, double* e_coul, double* e_gb, T* force,

@@ -650,7 +650,7 @@ __global__ __launch_bounds__(kWide * kTile) void k_chain_wide(const WorkItem* __
     __shared__ ChainWide<T> L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kTile), lane = threadIdx.x % kTile;
     if ((int)blockIdx.x >= n_items) {
-        if (threadIdx.x < 256) sum_energies<T>(po.sums[blockIdx.x - n_items], wk, po.e_coul, po.e_gb);
+        sum_energies<T>(po.sums, blockIdx.x - n_items, wk, po.e_coul, po.e_gb);
         return;
     }
     const WorkItem w = items[blockIdx.x];

@@ -37,3 +37,28 @@ def test_energy_sums_over_spans(prec, tol):
         half = w[off[b]:off[b + 1]]
         assert abs(E[b] - half.sum()) <= tol * max(scale[b], np.abs(half).sum()), b
     assert E[3] == 0.0
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+def test_energy_sums_of_small_systems(prec):
+    # systems of up to 256 atoms are summed a wavefront each: the same values, bit for
+    # bit, as beside a system of 257, where each has a workgroup; from every launch that
+    # sums them
+    sizes = [1, 256, 63, 64, 65, 255, 128, 2]
+    systems = [synth.make_system(160 + k, n, 18.0 * (max(n, 8) / 2500.0) ** (1 / 3)) for k, n in enumerate(sizes)]
+    large = synth.make_system(170, 257, 18.0 * (257 / 2500.0) ** (1 / 3))
+    p, got = params_pair()[0], []
+    for batch_systems in (systems, systems + [large]):
+        for kw in ({}, {"j_blocks": 1}):
+            g, batch, _, atoms = build(batch_systems, prec)
+            off = np.insert(batch.atom_offset, 3, batch.atom_offset[3]).astype(np.int32)   # an empty system
+            plan = g.Plan(off, prec, j_blocks_per_item=kw.get("j_blocks"))
+            for single in (False, True):
+                plan.set_single_launch(single)
+                full = g.evaluate(plan, atoms, p)
+                few = g.evaluate(plan, atoms, p, force=False, dEdq=False, dEdrho=False)
+                for out in (full, few):
+                    got.append(torch.stack([out["e_coul"][:9], out["e_gb"][:9]]))
+    assert got[0][0, 3] == 0.0 and got[0][1, 3] == 0.0 and bool((got[0][1, 1:3] != 0.0).all())
+    for other in got[1:]:
+        assert torch.equal(got[0], other)
