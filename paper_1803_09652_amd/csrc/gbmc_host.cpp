@@ -60,10 +60,15 @@ constexpr int64_t kLongItemTiles = int64_t(1) << 19;
 //   FP64 descreening  820 24.3 / 18.5, 1128 24.3 / 20.5, 2016 26.3 / 29.0
 //   FP64 energy       136 16.8 / 15.6,  288 17.1 / 19.0
 //   FP64 chain        820 32.9 / 26.6, 1128 33.0 / 31.8, 2016 36.3 / 49.7
-int64_t wide_items(gbmc_precision prec, int pass)
+// Where no system has a second block (`single`) every tile is a diagonal one, which
+// the walk does in half the steps; in FP64 the lines of the descreening and chain
+// passes lie lower there.  Whole evaluations of systems of 8 atoms, whose tiles hold the
+// fewest overlapping pairs: 896 systems 55.6 / 56.6, 1152 59.2 / 71.7 (896 of 64 atoms
+// 74.8 / 66.7); FP32 gains up to the lines above (1,152 systems of 8 atoms 45.3 -> 43.7).
+int64_t wide_items(gbmc_precision prec, int pass, bool single)
 {
-    static const int64_t most[2][GBMC_N_PASSES] = {{1536, 320, 896}, {1536, 192, 1152}};
-    return most[prec == GBMC_FP64 ? 1 : 0][pass];
+    static const int64_t most[3][GBMC_N_PASSES] = {{1536, 320, 896}, {1536, 192, 1152}, {1024, 192, 896}};
+    return most[prec != GBMC_FP64 ? 0 : single ? 2 : 1][pass];
 }
 
 // Queued launch: the polls (each after a short sleep, about a microsecond
@@ -523,8 +528,11 @@ gbmc_status gbmc_plan_create(gbmc_plan** out, int32_t n_systems, const int32_t* 
         p->n_atoms = n_systems > 0 ? host_atom_offset[n_systems] : 0;
         p->prec = precision;
         p->tuning = t;
+        bool single = true;
+        for (int32_t b = 0; b < n_systems; ++b)
+            single = single && host_atom_offset[b + 1] - host_atom_offset[b] <= kTile;
         for (int k = 0; k < GBMC_N_PASSES; ++k)
-            p->wide[k] = !tuning && (int64_t)items[k].size() <= wide_items(precision, k);
+            p->wide[k] = !tuning && (int64_t)items[k].size() <= wide_items(precision, k, single);
         p->offset.assign(host_atom_offset, host_atom_offset + n_systems + 1);
         if (n_systems == 0) p->offset.assign(1, 0);
         std::vector<BlockSpan> blocks;

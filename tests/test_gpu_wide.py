@@ -71,3 +71,16 @@ def test_wide_overflow_flag():
     assert g.check_overflow(plan)
     g.evaluate(plan, g.Atoms.from_batch(plan, batch), params_pair()[0])
     assert not g.check_overflow(plan)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n_systems", [896, 897, 1024, 1025])
+def test_batches_of_single_blocks(prec, n_systems):
+    # no tile off the diagonal: on both sides of the lines of such batches
+    few = _systems([8, 3, 17, 64])
+    systems = [few[k % 4] for k in range(n_systems)]
+    g, batch, wide, atoms = build(systems, prec)
+    _, _, walk, walk_atoms = build(systems, prec, j_blocks=1)
+    a, b = g.evaluate(wide, atoms, params_pair()[0]), g.evaluate(walk, walk_atoms, params_pair()[0])
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
