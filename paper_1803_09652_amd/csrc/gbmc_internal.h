@@ -48,11 +48,13 @@ struct BlockSpan {
 
 // One work item of a cutoff pass, written on the device: i block I of the
 // system at [base, base + n) against the j blocks J0 + k, k < J1 - J0 <= 64,
-// whose bit k is set in the mask (mask_hi:mask_lo); at most kCutTiles bits.
+// whose bit k is set in the mask (mask_hi:mask_lo); at most kCutTiles bits.  Bit
+// kCutRare + t of J1: in the item's t-th tile few balls straddle the descreening sphere.
 struct CutItem {
     int32_t base, n, I, J0, J1, blk0;
     uint32_t mask_lo, mask_hi;
 };
+constexpr int kCutRare = 24;             // (a system has at most 65,535 blocks)
 constexpr int kCutTiles = 4;
 constexpr int kCutChunk = 64;            // j blocks per chunk of a block row
 

@@ -665,7 +665,11 @@ __device__ __forceinline__ void chain_pair_cut(double r, double r2, double invr,
 // drops, descreening 1014 -> 453 us and chain pass 1346 -> 922 us on 100,000
 // atoms at c = 15 A (the energy pass, which gains from box_gap alone, 601 -> 480).  It is also ten
 // times more accurate in FP32, since J's leading terms cancel in closed form.
-// SEP (separated tiles): no overlap test, and the short fits.
+// SEP (separated tiles): no overlap test, and the short fits.  RARE: a step in which no
+// ball reaches beyond c skips these terms, all zero there.  Without it a system well
+// inside c paid for them at every pair: 3,000 atoms within 40 A, FP64, 380 us an
+// evaluation, with it 322 (the closed form behind such a test: 320); 20,000 atoms at
+// c = 25 A in FP32 671 -> 618.
 __device__ __forceinline__ float cut_l(float e) { return hct_cut_l(e); }
 __device__ __forceinline__ double cut_l(double e) { return hct_cut_l64(e); }
 __device__ __forceinline__ float cut_a(float e) { return hct_cut_a(e); }
@@ -699,7 +703,15 @@ __device__ __forceinline__ void cut_beyond_grad(T r, T invr, T S, T c, T ic, T& 
     g -= T(0.25) * invr * ic * q;
 }
 
-template <bool SEP, typename T>
+// Whether a ball of the pair of some lane reaches beyond c.  On a RARE tile pairs lie
+// within 1.25 c (k_cut_items), so r >= 2 c is a lane past the end, whose terms are dropped.
+template <typename T>
+__device__ __forceinline__ bool cut_any(T r, T Si, T Sj, T c)
+{
+    return __builtin_amdgcn_ballot_w64(((r - c + Sj > T(0)) | (r - c + Si > T(0))) & (r < T(2) * c)) != 0ull;
+}
+
+template <bool SEP, bool RARE, typename T>
 __device__ __forceinline__ void radii_pair_cutf(T xi, T yi, T zi, T xj, T yj, T zj, T rti, T Si, T rtj,
                                                 T Sj, T c, T ic, T& hij, T& hji)
 {
@@ -715,12 +727,13 @@ __device__ __forceinline__ void radii_pair_cutf(T xi, T yi, T zi, T xj, T yj, T 
         if (!((r - Sj >= rti) & (yij <= y_max<T>()))) hij = slow_H(r, invr, rti, Sj);
         if (!((r - Si >= rtj) & (yji <= y_max<T>()))) hji = slow_H(r, invr, rtj, Si);
     }
+    if (RARE && !cut_any(r, Si, Sj, c)) return;
     hij = r - Sj >= c ? T(0) : hij - cut_beyond(r, invr, Sj, c, ic);
     hji = r - Si >= c ? T(0) : hji - cut_beyond(r, invr, Si, c, ic);
 }
 
-template <bool SEP, typename T>
-__device__ __forceinline__ void chain_pair_cutf(T r, T r2, T invr, T rti, T Si, T rtj, T Sj, T bi, T bj,
+template <bool SEP, bool RARE, typename T>
+__device__ __forceinline__ void chain_pair_cutf(bool few, T r, T r2, T invr, T rti, T Si, T rtj, T Sj, T bi, T bj,
                                                 T c, T ic, T& dEdr, T& gij2, T& gji2, T& dri, T& drj)
 {
     const T u = invr * invr;
@@ -760,12 +773,14 @@ __device__ __forceinline__ void chain_pair_cutf(T r, T r2, T invr, T rti, T Si, 
             drj = out_ji ? drj : fma(bj, g[1], drj);
         }
     }
-    cut_beyond_grad(r, invr, Sj, c, ic, aij, gij2);
-    cut_beyond_grad(r, invr, Si, c, ic, aji, gji2);
-    aij = out_ij ? T(0) : aij;
-    aji = out_ji ? T(0) : aji;
-    gij2 = out_ij ? T(0) : gij2;
-    gji2 = out_ji ? T(0) : gji2;
+    if (!RARE || !few || cut_any(r, Si, Sj, c)) {
+        cut_beyond_grad(r, invr, Sj, c, ic, aij, gij2);
+        cut_beyond_grad(r, invr, Si, c, ic, aji, gji2);
+        aij = out_ij ? T(0) : aij;
+        aji = out_ji ? T(0) : aji;
+        gij2 = out_ij ? T(0) : gij2;
+        gji2 = out_ji ? T(0) : gji2;
+    }
     dEdr = -u * fma(bi, aij, bj * aji);
 }
 
@@ -1065,21 +1080,25 @@ __global__ __launch_bounds__(256) void k_block_bounds(const BlockSpan* __restric
 // not (integer sums, one rounding unit per tile and per item's i sums).
 constexpr int kCutWaves = 16;
 
-__device__ __forceinline__ void write_cut_items(unsigned long long mask, const WorkItem& w,
-                                                int lane, int base, CutItem* __restrict__ out,
-                                                int cap)
+__device__ __forceinline__ void write_cut_items(unsigned long long mask, unsigned long long rare,
+                                                const WorkItem& w, int lane, int base,
+                                                CutItem* __restrict__ out, int cap)
 {
     const int n_sub = (__popcll(mask) + kCutTiles - 1) / kCutTiles;
     if (lane < n_sub && base + lane < cap) {
         // the set bits of ranks [lane kCutTiles, (lane + 1) kCutTiles)
         unsigned long long m = mask, sub = 0ull;
+        int few = 0;
         for (int rank = 0; m; ++rank) {
             const unsigned long long low = m & (~m + 1ull);
             m ^= low;
-            if (rank / kCutTiles == lane) sub |= low;
+            if (rank / kCutTiles == lane) {
+                sub |= low;
+                few |= (rare & low) ? 1 << (kCutRare + rank % kCutTiles) : 0;
+            }
         }
         CutItem c;
-        c.base = w.base; c.n = w.n; c.I = w.I; c.J0 = w.J0; c.J1 = w.J1; c.blk0 = w.blk0;
+        c.base = w.base; c.n = w.n; c.I = w.I; c.J0 = w.J0; c.J1 = w.J1 | few; c.blk0 = w.blk0;
         c.mask_lo = (uint32_t)sub;
         c.mask_hi = (uint32_t)(sub >> 32);
         out[base + lane] = c;
@@ -1095,26 +1114,31 @@ __global__ __launch_bounds__(kTile * kCutWaves) void k_cut_items(
     __shared__ int base[2];
     const int wave = threadIdx.x / kTile, lane = threadIdx.x % kTile;
     const int ci = blockIdx.x * kCutWaves + wave;
-    unsigned long long m0 = 0ull, m1 = 0ull;
+    unsigned long long m0 = 0ull, m1 = 0ull, mr = 0ull;
     WorkItem w{};
     if (ci < n_chunks) {                         // wave-uniform; every wave reaches the barriers
         w = chunks[ci];
         const Q4<float> bI = bnd[w.blk0 + w.I];
         const float sI = smax[w.blk0 + w.I];
         const int J = w.J0 + lane;
-        bool n0 = false, n1 = false;
+        bool n0 = false, n1 = false, rare = false;
         if (J < w.J1) {
             const Q4<float> bJ = bnd[w.blk0 + J];
             // the larger of two lower bounds: spheres are the tighter one where
             // blocks lie across a corner, boxes elsewhere (together 20 % fewer
             // tiles than spheres alone in the compact-block order, 29 % in the
             // Morton order, on 20,000 atoms at 16 A)
-            const float gap = fmaxf(block_gap(bI, bJ), box_gap(box, w.blk0 + w.I, w.blk0 + J));
+            const float sphere = block_gap(bI, bJ), both = bI.w + bJ.w;
+            const float gap = fmaxf(sphere, box_gap(box, w.blk0 + w.I, w.blk0 + J));
+            // (centre distance + 0.8 of the two radii: at most a few per cent of the pairs
+            // of two even balls lie farther apart)
+            rare = sphere + 1.8f * both < cR;
             n0 = cR > 0.0f && gap - fmaxf(sI, smax[w.blk0 + J]) < cR;
             n1 = cE > 0.0f && gap < cE;
         }
         m0 = __ballot(n0);
         m1 = __ballot(n1);
+        mr = __ballot(rare);
     }
     if (lane == 0) {
         cnt[0][wave] = (__popcll(m0) + kCutTiles - 1) / kCutTiles;
@@ -1132,8 +1156,8 @@ __global__ __launch_bounds__(kTile * kCutWaves) void k_cut_items(
         off0 += cnt[0][k];
         off1 += cnt[1][k];
     }
-    write_cut_items(m0, w, lane, off0, out0, cap);
-    write_cut_items(m1, w, lane, off1, out1, cap);
+    write_cut_items(m0, mr, w, lane, off0, out0, cap);
+    write_cut_items(m1, 0ull, w, lane, off1, out1, cap);
 }
 
 // Inclusive sum of v over the lanes of a full wave.
@@ -1170,6 +1194,7 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
     // separated blocks (tile_tier) skip the per-pair test and take short fits of H
     constexpr bool DEFER = !CUT;
     [[maybe_unused]] const T icR = CUT ? T(1) / cR : T(0);
+    int rare = CUT ? w.sys : 0;             // tiles in which few balls straddle the sphere
     T xi[R], yi[R], zi[R], rti[R], Si[R];
     bool vi[R];
 #pragma unroll
@@ -1219,6 +1244,8 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
     auto tile = [&](int J) {
         int Jn = J + 1;
         if constexpr (CUT) Jnext = Jn = next_tile(tmask, w.J0, w.J1, J + 1);
+        [[maybe_unused]] const bool few = rare & 1;
+        rare >>= 1;
         const int j = J * kTile + lane;
         const bool vj = j < w.n;
         T Sj;
@@ -1239,7 +1266,7 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
         int kstep = J == w.I ? 1 : 0;           // DEFER: walk step of the next pair
         unsigned long long dmask = 0ull;
         // KIND: the tier of the tile; with a cutoff 0 (any cutoff), 1 (cut_small
-        // tiles) and 2 (those separated)
+        // tiles) and 2 (those separated), and 3 and 4 the same with few straddling balls
         auto pair = [&](auto kind) {
             return [&](const JD& d, int r, bool act, T (&acc)[1], bool) {
                 constexpr int KIND = decltype(kind)::value;
@@ -1248,8 +1275,8 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
                     radii_pair_cut(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r], Si[r], d.p.w,
                                    d.S, cR, hij, hji);
                 } else if constexpr (CUT) {
-                    radii_pair_cutf<KIND == 2>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r],
-                                               Si[r], d.p.w, d.S, cR, icR, hij, hji);
+                    radii_pair_cutf<KIND % 2 == 0, (KIND > 2)>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z,
+                                                               rti[r], Si[r], d.p.w, d.S, cR, icR, hij, hji);
                 } else {
                     radii_pair_fast<KIND>(xi[r], yi[r], zi[r], d.p.x, d.p.y, d.p.z, rti[r], Si[r],
                                           d.p.w, d.S, act && vi[r], 1ull << kstep, hij, hji, dmask);
@@ -1266,7 +1293,12 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
             const int tier = J == w.I ? 0
                              : CUT || sizeof(T) == 4 ? blocks_separated(box, X, Y, GBMC_HCT_YFAR)
                                                      : tile_tier<1>(box, X, Y);
-            if (tier == 0)
+            if (CUT && few) {
+                if (tier == 0)
+                    walk_tile<T, 1>(lane, J == w.I, aj, load, pair(std::integral_constant<int, CUT ? 3 : 0>{}));
+                else
+                    walk_tile<T, 1>(lane, false, aj, load, pair(std::integral_constant<int, CUT ? 4 : 0>{}));
+            } else if (tier == 0)
                 walk_tile<T, 1>(lane, J == w.I, aj, load, pair(std::integral_constant<int, CUT ? 1 : 0>{}));
             else if (tier == 1)
                 walk_tile<T, 1>(lane, false, aj, load, pair(std::integral_constant<int, CUT ? 2 : 1>{}));
@@ -1337,12 +1369,13 @@ __device__ __forceinline__ void radii_item(const WorkItem& w, int lane, Q4<T>* s
 }
 
 // The compacted items of a cutoff pass, taken in a grid-stride loop (the
-// count is known on the device only).
+// count is known on the device only).  sys: the item's kCutRare bits.
 __device__ __forceinline__ WorkItem cut_work_item(const CutItem& c, unsigned long long& mask)
 {
     mask = ((unsigned long long)c.mask_hi << 32) | c.mask_lo;
     WorkItem w;
-    w.base = c.base; w.n = c.n; w.sys = 0; w.I = c.I; w.J0 = c.J0; w.J1 = c.J1; w.rows = 1;
+    w.base = c.base; w.n = c.n; w.sys = c.J1 >> kCutRare; w.I = c.I; w.J0 = c.J0;
+    w.J1 = c.J1 & ((1 << kCutRare) - 1); w.rows = 1;
     w.blk0 = c.blk0;
     return w;
 }
@@ -1935,6 +1968,7 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
     // does not depend on the order of the rounds).
     constexpr bool DEFER = !CUT;
     [[maybe_unused]] const T icR = CUT ? T(1) / cR : T(0);
+    int rare = CUT ? w.sys : 0;             // tiles in which few balls straddle the sphere
     T xi[R], yi[R], zi[R], rti[R], Si[R], Bi[R], si[R];
     bool vi[R];
 #pragma unroll
@@ -1998,6 +2032,8 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
         constexpr bool FIRST = decltype(first_tag)::value;
         int Jn = J + 1;
         if constexpr (CUT) Jnext = Jn = next_tile(tmask, w.J0, w.J1, J + 1);
+        [[maybe_unused]] const bool few = rare & 1;
+        rare >>= 1;
         const int j = J * kTile + lane;
         const bool vj = j < w.n;
         tail(J, pj, bj, gj, gfj, drj);
@@ -2018,7 +2054,10 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
         unsigned long long dmask[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) dmask[r] = 0ull;
-        // KIND as in the descreening pass
+        // KIND as in the descreening pass; FP32 walks ask for `few` at every step instead of
+        // having two more walks, which took 935 us instead of 893 on 100,000 atoms (the
+        // descreening pass loses 40 us of 445 by asking)
+        [[maybe_unused]] constexpr bool kAsk = sizeof(T) == 4;
         auto pair = [&](auto kind) {
             return [&](const JD& d, int r, bool act, T (&acc)[4], bool) {
                 constexpr int KIND = decltype(kind)::value;
@@ -2035,8 +2074,9 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
                     chain_pair_cut(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, cR, dEdr, gij2,
                                    gji2, dri[r], acc[3]);
                 } else if constexpr (CUT) {
-                    chain_pair_cutf<KIND == 2>(rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, cR,
-                                               icR, dEdr, gij2, gji2, dri[r], acc[3]);
+                    chain_pair_cutf<KIND % 2 == 0, (kAsk || KIND > 2)>(
+                        few, rr, r2, invr, rti[r], Si[r], p.w, b.x, bi_, bj_, cR, icR, dEdr, gij2, gji2,
+                        dri[r], acc[3]);
                 } else {
                     // only pairs of a real i atom are marked (padding lanes sit far
                     // apart, so none of theirs needs the closed form anyway)
@@ -2066,7 +2106,10 @@ __device__ __forceinline__ void chain_item(const WorkItem& w, int lane, Q4<T>* s
             walk(std::integral_constant<int, 0>{}, diagonal);
         } else {
             const int tier = diagonal ? 0 : tile_tier<R>(wk.box, X, Y);
-            if (tier == 0) walk(std::integral_constant<int, CUT ? 1 : 0>{}, diagonal);
+            if (CUT && !kAsk && few) {
+                if (tier == 0) walk(std::integral_constant<int, CUT ? 3 : 0>{}, diagonal);
+                else walk(std::integral_constant<int, CUT ? 4 : 0>{}, false);
+            } else if (tier == 0) walk(std::integral_constant<int, CUT ? 1 : 0>{}, diagonal);
             else if (CUT || tier == 1) walk(std::integral_constant<int, CUT ? 2 : 1>{}, false);
             else if constexpr (!CUT) walk(std::integral_constant<int, 2>{}, false);
         }
