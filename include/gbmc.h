@@ -93,9 +93,10 @@ typedef struct {
  * descreening 1 / 2, energy 1 / 4, chain 1 / 4, and for FP32 batches of at
  * least 2^19 tiles (sum over systems of nb (nb + 1) / 2, nb = ceil(n / 64))
  * energy and chain 4 / 1; FP64 1 / 2 for all three passes.  With tuning NULL a
- * pass of few items (FP32: at most 1536, 320 and 896, FP64: 1536, 192 and 1152)
- * shares the steps of every item among the wavefronts of a workgroup, with the
- * same results bit for bit. */
+ * pass of few items (FP32: at most 1536, 320 and 896, FP64: 1536, 192 and 1152,
+ * or 1024, 192 and 896 where no system has more than 64 atoms) shares the steps
+ * of every item among the wavefronts of a workgroup, with the same results bit
+ * for bit; no explicit tuning asks for that. */
 enum { GBMC_PASS_RADII = 0, GBMC_PASS_ENERGY = 1, GBMC_PASS_CHAIN = 2, GBMC_N_PASSES = 3 };
 typedef struct {
     int32_t j_blocks_per_item[GBMC_N_PASSES];

@@ -426,6 +426,10 @@ static void plan_schedule(int32_t n_systems, const int32_t* off, gbmc_precision 
 // touch every system of the batch, so this holds while its inputs stay in an
 // XCD's 4 MB of L2: 16 of 4,001 (64,016 atoms) 456 -> 446 us, 24 of them 644 -> 645,
 // 32 of them (energies only) 325.5 -> 334.5; long items of 646,341 atoms lose 4 %.
+// With the atoms in the order in which they came every tile holds overlapping pairs;
+// only the rows still differ, and the list is as good or better: whole evaluations of
+// one system of 10,000 222 -> 206 us, of 20,001 750 -> 655, 24 of 65-3,777 242 -> 233, 12
+// of 4,001 and 16 of 2,500 even, FP64 even.
 constexpr int32_t kNearAtoms = 65536;
 
 static std::vector<WorkItem> near_first(std::vector<WorkItem> items)
